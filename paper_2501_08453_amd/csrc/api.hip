@@ -171,12 +171,12 @@ size_t fwd_tail_bytes(const vc_jointattn_desc* d, int64_t n) {
 }
 size_t fwd_ws_bytes(const vc_jointattn_desc* d, int64_t n) { return tiles_bytes(d, n) + fwd_tail_bytes(d, n); }
 
-// Backward workspace: -D | LSE*log2(e) | Q^T tiles | dO^T tiles | K^T tiles | tail partials.
+// Backward workspace: -D | -LSE/c | fp32 dQ accumulator (the size of two sets of token
+// tiles, >= 4 bytes per element of dq) | K^T tiles | tail partials.
 struct BwdWorkspace {
   float* dd;
-  float* lse2;
-  __bf16* qt;
-  __bf16* dot;
+  float* nls;
+  float* dq_acc;
   __bf16* kt;
 };
 
@@ -191,8 +191,7 @@ BwdWorkspace split_bwd_ws(const vc_jointattn_desc* d, int64_t n, void* ws) {
   char* p = static_cast<char*>(ws);
   const size_t rb = rows_bytes(d, n), tb = tiles_bytes(d, n);
   return BwdWorkspace{reinterpret_cast<float*>(p), reinterpret_cast<float*>(p + rb),
-                      reinterpret_cast<__bf16*>(p + 2 * rb), reinterpret_cast<__bf16*>(p + 2 * rb + tb),
-                      reinterpret_cast<__bf16*>(p + 2 * rb + 2 * tb)};
+                      reinterpret_cast<float*>(p + 2 * rb), reinterpret_cast<__bf16*>(p + 2 * rb + 2 * tb)};
 }
 
 // Spatial branch: split of the text key blocks' video query tiles into chunks of about one
@@ -308,11 +307,8 @@ size_t vc_spatialattn_bwd_workspace_bytes(const vc_jointattn_desc* desc) {
 
 namespace {
 
-// Token-major copies a backward's stage 1 makes: none (every key's dQ share added in the
-// key-stationary pass), of k (read by the dQ pass), or of q, dout and k (the separate passes).
-enum class StageTiles { kNone, kKeys, kAll };
 vc_status prepare_impl(const vc_jointattn_desc* desc, const void* q, const void* k, const void* o, const float* lse,
-                       const void* dout, void* workspace, size_t workspace_bytes, void* stream, StageTiles tiles);
+                       const void* dout, void* workspace, size_t workspace_bytes, void* stream, bool key_tiles);
 
 // Joint attention (frame_len 0) or the spatial branch (frame_len = tokens per frame).
 vc_status fwd_impl(const vc_jointattn_desc* desc, const void* q, const void* k, const void* v,
@@ -393,20 +389,18 @@ vc_status vc_jointattn_bwd_prepare(const vc_jointattn_desc* desc, const void* q,
   int64_t n = 0;
   const vc_status st = check_desc(desc, &n);
   if (st != VC_OK) return st;
-  const StageTiles tiles = desc->deterministic     ? StageTiles::kAll
-                           : all_keys_fused(desc, n) ? StageTiles::kNone
-                                                     : StageTiles::kKeys;
-  return prepare_impl(desc, q, k, o, lse, dout, workspace, workspace_bytes, stream, tiles);
+  return prepare_impl(desc, q, k, o, lse, dout, workspace, workspace_bytes, stream,
+                      desc->deterministic || !all_keys_fused(desc, n));
 }
 
 }  // extern "C"
 
 namespace {
 
-// Backward stage 1 and the token-major copies `tiles` asks for: those of q and dout are read
-// by the separate dK/dV pass only, that of k by a dQ pass over key tiles.
+// Backward stage 1 and, with `key_tiles`, the token-major copy of k that a dQ pass over key
+// tiles reads (none when every key's dQ share is added in the key-stationary pass).
 vc_status prepare_impl(const vc_jointattn_desc* desc, const void* q, const void* k, const void* o, const float* lse,
-                       const void* dout, void* workspace, size_t workspace_bytes, void* stream, StageTiles tiles) {
+                       const void* dout, void* workspace, size_t workspace_bytes, void* stream, bool key_tiles) {
   int64_t n = 0;
   vc_status st = check_desc(desc, &n);
   if (st != VC_OK) return st;
@@ -417,13 +411,11 @@ vc_status prepare_impl(const vc_jointattn_desc* desc, const void* q, const void*
   const BwdWorkspace w = split_bwd_ws(desc, n, workspace);
   const int B = desc->batch, H = desc->heads, D = desc->head_dim, N = (int)n;
   hipStream_t s = as_stream(stream);
-  if (vcja::launch_bwd_prepare(bf(o), lse, bf(dout), w.dd, w.lse2, B, H, N, ntiles(n) * vcja::kTileTok, D, s) !=
+  if (vcja::launch_bwd_prepare(bf(o), lse, bf(dout), w.dd, w.nls, B, H, N, ntiles(n) * vcja::kTileTok, D,
+                               scale_of(desc), s) !=
       hipSuccess)
     return VC_ERR_HIP;
-  if (tiles == StageTiles::kAll && (vcja::launch_token_tiles(bf(q), w.qt, B, H, N, D, s) != hipSuccess ||
-                                    vcja::launch_token_tiles(bf(dout), w.dot, B, H, N, D, s) != hipSuccess))
-    return VC_ERR_HIP;
-  if (tiles != StageTiles::kNone && vcja::launch_token_tiles(bf(k), w.kt, B, H, N, D, s) != hipSuccess)
+  if (key_tiles && vcja::launch_token_tiles(bf(k), w.kt, B, H, N, D, s) != hipSuccess)
     return VC_ERR_HIP;
   return VC_OK;
 }
@@ -443,8 +435,8 @@ vc_status dkdv_impl(const vc_jointattn_desc* desc, const void* q, const void* k,
       VC_OK)
     return st;
   if ((st = check_device()) != VC_OK) return st;
-  // The separate stages 2 and 3 read the token-major copies, which stage 1 makes only for
-  // the deterministic backward.
+  // The separate stages 2 and 3 belong to the deterministic backward: stage 1 makes the
+  // token-major copy of k that stage 3 reads over all keys only there.
   if (staged && !desc->deterministic) return VC_ERR_UNSUPPORTED;
   const BwdWorkspace w = split_bwd_ws(desc, n, workspace);
   vcja::DkdvArgs a{};
@@ -462,17 +454,13 @@ vc_status dkdv_impl(const vc_jointattn_desc* desc, const void* q, const void* k,
   a.k = bf(k);
   a.v = bf(v);
   a.dout = bf(dout);
-  a.qt = w.qt;
-  a.dot = w.dot;
-  a.lse2 = w.lse2;
+  a.nls = w.nls;
   a.dd = w.dd;
   a.text_len = text_len;
   a.key_mask = key_mask;
   a.dk = static_cast<__bf16*>(dk);
   a.dv = static_cast<__bf16*>(dv);
-  // Fused dQ: the fp32 accumulator takes the place of the transposed Q and dO tiles, which
-  // the fused backward does not make (2 tile sets >= 4 bytes per element of dq).
-  a.dq_acc = fused ? reinterpret_cast<float*>(w.qt) : nullptr;
+  a.dq_acc = fused ? w.dq_acc : nullptr;
   a.dq_blocks = !fused ? 0 : spatial ? std::numeric_limits<int>::max() : fused_dq_blocks(desc, n);
   a.B = desc->batch;
   a.H = desc->heads;
@@ -504,7 +492,7 @@ vc_status dq_impl(const vc_jointattn_desc* desc, const void* q, const void* k, c
   if (fused) {
     if (spatial || all_keys_fused(desc, n)) {
       hipStream_t s = as_stream(stream);
-      if (vcja::launch_dq_from_acc(reinterpret_cast<const float*>(w.qt), static_cast<__bf16*>(dq),
+      if (vcja::launch_dq_from_acc(w.dq_acc, static_cast<__bf16*>(dq),
                                    (size_t)desc->batch * n * desc->heads * desc->head_dim, scale_of(desc),
                                    s) != hipSuccess)
         return VC_ERR_HIP;
@@ -515,14 +503,14 @@ vc_status dq_impl(const vc_jointattn_desc* desc, const void* q, const void* k, c
       return VC_OK;
     }
     a.kt_min = fused_dq_blocks(desc, n) * (vcja::kDkdvKeys / vcja::kTileTok);
-    a.dq_acc = reinterpret_cast<const float*>(w.qt);
+    a.dq_acc = w.dq_acc;
   }
   a.q = bf(q);
   a.k = bf(k);
   a.v = bf(v);
   a.dout = bf(dout);
   a.kt = w.kt;
-  a.lse2 = w.lse2;
+  a.nls = w.nls;
   a.dd = w.dd;
   a.text_len = text_len;
   a.key_mask = key_mask;
@@ -560,14 +548,14 @@ vc_status bwd_impl(const vc_jointattn_desc* desc, const void* q, const void* k, 
   // the others), the spatial branch for every key block (a video query row gets the shares
   // of 16 key blocks at 720p, so the atomics are few); neither past 32-bit dQ offsets.
   if (!desc->deterministic && (spatial ? dq_offsets_fit(desc, n) : fused_dq_blocks(desc, n) > 0)) {
-    const StageTiles tiles = (spatial || all_keys_fused(desc, n)) ? StageTiles::kNone : StageTiles::kKeys;
-    if ((st = prepare_impl(desc, q, k, o, lse, dout, workspace, workspace_bytes, stream, tiles)) != VC_OK ||
+    if ((st = prepare_impl(desc, q, k, o, lse, dout, workspace, workspace_bytes, stream,
+                           !spatial && !all_keys_fused(desc, n))) != VC_OK ||
         (st = dkdv_impl(desc, q, k, v, dout, text_len, key_mask, dk, dv, workspace, workspace_bytes, stream,
                         spatial, true)) != VC_OK)
       return st;
     return dq_impl(desc, q, k, v, dout, text_len, key_mask, dq, workspace, workspace_bytes, stream, spatial, true);
   }
-  if ((st = prepare_impl(desc, q, k, o, lse, dout, workspace, workspace_bytes, stream, StageTiles::kAll)) != VC_OK)
+  if ((st = prepare_impl(desc, q, k, o, lse, dout, workspace, workspace_bytes, stream, true)) != VC_OK)
     return st;
   if ((st = dkdv_impl(desc, q, k, v, dout, text_len, key_mask, dk, dv, workspace, workspace_bytes, stream,
                       spatial)) != VC_OK)

@@ -1,28 +1,30 @@
 // Backward joint text-video attention for gfx950.
 //
-// Prepare: per query row, -D_i = -<dO_i, O_i> and LSE_i*log2(e) in fp32, padded
-//   to whole tiles of 64 rows (padding rows get LSE = +inf so that their
-//   probabilities vanish, and D = 0). D is stored negated so that dP - D is
-//   what the dP accumulator holds when it starts from -D.
+// Prepare: per query row, -D_i = -<dO_i, O_i> and -LSE_i / c in fp32, padded
+//   to whole tiles of 64 rows (padding rows get -inf for the latter so that their
+//   probabilities vanish, and D = 0). So dP - D is what the dP accumulator holds
+//   when it starts from -D, and S - LSE / c (P = exp2 of it times c log2(e)) what
+//   the score accumulator holds when it starts from -LSE / c.
 // dK/dV (key-stationary): one workgroup of eight waves owns 256 keys of one
 //   (sample, head), each wave 32, with K and V of its keys in registers and
-//   dK^T, dV^T accumulated in registers. It walks over all query tiles of 64,
-//   whose row-major Q and dO tiles, LSE and D are copied asynchronously
-//   global -> LDS into a two-stage ring one tile ahead; one barrier per tile. Per
-//   tile it recomputes S = Q K^T and P = exp2(S c log2(e) - LSE log2(e)), forms
-//   dP - D = -D + dO V^T and dS = P o (dP - D) with the matrix cores, and
-//   accumulates dV^T += dO^T P and dK^T += Q^T dS straight from the accumulator
-//   layout (lane column = key). The transposed operands Q^T, dO^T come either
-//   from transposed token tiles made by a reformatting pass (separate dQ pass)
-//   or, with dQ fused in, from the row-major tiles through transposing LDS reads.
+//   dK^T, dV^T accumulated in registers. It walks over all query tiles of 32,
+//   whose row-major Q and dO rows are copied asynchronously global -> LDS into a
+//   two-stage ring one tile ahead; one barrier per tile. Per tile it recomputes
+//   S = Q K^T and P = exp2((S - LSE / c) c log2(e)), forms dP - D = -D + dO V^T
+//   and dS = P o (dP - D) with the matrix cores, and accumulates dV^T += dO^T P and
+//   dK^T += Q^T dS straight from the accumulator layout (lane column = key). The
+//   transposed operands Q^T, dO^T come from the row-major rows through transposing
+//   LDS reads. What bounds it: each wave's in-order stream of matrix-core ops, LDS
+//   reads and vector arithmetic, at the power-limited matrix rate; so the reads are
+//   placed ahead of their products and the arithmetic between them by hand, and the
+//   copies cost scalar arithmetic only. 24 heads x 57,856 tokens, D = 128, no dQ:
+//   68.4 -> 62 ms; with dQ of 65% of the keys 97.2 -> 90 ms (one box).
 // dQ, fused (the default for joint attention at head_dim 128): in the workgroups
 //   of the first key blocks (a fraction set by the host), after the dK/dV products
-//   of a tile, the waves exchange dS^T through LDS (the first 32 queries in a
-//   region of its own, the others over the tile's Q|dO region, dead by then) and
-//   each wave computes one 32x32 block of the tile's dQ / scale = dS K over the
-//   workgroup's 256 keys, with K^T held in LDS for the workgroup's lifetime. The
-//   block is added to an fp32 accumulator with atomics one tile later (so that
-//   the wait for the next tile's copies does not also wait for them), and the
+//   of a tile, the waves exchange dS^T through LDS and, one tile later, D/32 of
+//   them (in turns) each compute one 32x32 block of the tile's dQ / scale = dS K
+//   over the workgroup's 256 keys, with K^T held in LDS for the workgroup's
+//   lifetime, and add it to an fp32 accumulator with atomics; the
 //   workgroups of each XCD start their walk at a different query tile so that
 //   concurrent atomics spread over the accumulator. For those keys S and dP are
 //   computed once per (query, key) pair; the atomic traffic (fp32 dQ rows per key
@@ -48,7 +50,7 @@ namespace {
 constexpr int kDkdvWaves = 8;
 constexpr int kBKV = 32 * kDkdvWaves;  // keys per dK/dV workgroup
 static_assert(kBKV == kDkdvKeys, "dK/dV key block");
-constexpr int kBQ = kTileTok;  // queries per dK/dV tile
+constexpr int kBQ = 32;                // queries per dK/dV tile
 constexpr int kDqWaves = 8;
 constexpr int kDqBM = 32 * kDqWaves;  // queries per dQ workgroup
 constexpr int kBN = kTileTok;         // keys per dQ tile
@@ -57,8 +59,8 @@ template <int D>
 __global__ __launch_bounds__(256) void bwd_prepare_kernel(const __bf16* __restrict__ o,
                                                           const float* __restrict__ lse,
                                                           const __bf16* __restrict__ dout,
-                                                          float* __restrict__ dd, float* __restrict__ lse2, int B,
-                                                          int H, int N, int Npad) {
+                                                          float* __restrict__ dd, float* __restrict__ nls, int B,
+                                                          int H, int N, int Npad, float inv_scale) {
   constexpr int CPR = D / 8;  // 16-byte chunks per (token, head) row
   const size_t gid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   const size_t rows = (size_t)B * N * H;
@@ -81,7 +83,7 @@ __global__ __launch_bounds__(256) void bwd_prepare_kernel(const __bf16* __restri
     const size_t bh = (size_t)b * H + h;
     const float x = lse[bh * N + n];
     dd[bh * Npad + n] = -sum;
-    lse2[bh * Npad + n] = (x == -INFINITY) ? INFINITY : x * kLog2e;
+    nls[bh * Npad + n] = (x == -INFINITY) ? -INFINITY : -x * inv_scale;
   }
   // Padding rows [N, Npad) of every (sample, head).
   const size_t pads = (size_t)B * H * (Npad - N);
@@ -89,31 +91,34 @@ __global__ __launch_bounds__(256) void bwd_prepare_kernel(const __bf16* __restri
     const size_t bh = gid / (Npad - N);
     const int n = N + (int)(gid % (Npad - N));
     dd[bh * Npad + n] = 0.0f;
-    lse2[bh * Npad + n] = INFINITY;
+    nls[bh * Npad + n] = -INFINITY;
   }
 }
 
-// LDS layout of the dK/dV kernel. A stage holds one query tile: Q | dO (row-major) |
-// Q^T | dO^T (transposed tiles; not with dQ fused) | LSE*log2e[64] | -D[64]. With dQ
-// fused, K^T of the workgroup's keys ([D][256 + 8] bf16) follows the two stages, then
-// dS^T of the tile's first 32 queries ([256 keys][32] bf16); dS^T of the other 32 is
-// written over the current stage's Q | dO region once every wave is done with it.
+// LDS layout of the dK/dV kernel. A stage holds one tile of 32 queries: their Q rows, their
+// dO rows (swizzled rows in perm_row order); two stages. Two buffers of -LSE/c[256] |
+// -D[256] follow, for 8 tiles each (copied once per 8 tiles: a 32-query copy per tile, by
+// two of the waves, held up every tile's barrier). With dQ fused, K^T of the workgroup's keys ([D][256 + 8] bf16) and two buffers of a tile's dS^T
+// ([256 keys][32] bf16) follow, read by the dQ products.
 // dS^T rows are 72 bytes (32 queries + 4 pad), and key 32u + 4j + e sits in row
 // 32u + 8e + j: the writes (32 consecutive keys, one per lane) hit 64 distinct banks, the
 // transposing reads (4 consecutive keys x 32 queries per half-wave) too, as the 4 keys'
 // rows lie 8 apart; every address is a per-lane base plus an immediate offset.
 template <int D, bool FUSED>
 struct DkdvLds {
-  static constexpr int RT = RowTile<D>::kBytes;
-  static constexpr int TT = FUSED ? 0 : (int)tile_elems(D) * 2;
-  static constexpr int STAGE = 2 * RT + 2 * TT + 512;
-  static constexpr int KTS = (kBKV + 8) * 2;  // K^T row stride (bytes)
-  static constexpr int DSS = (32 + 4) * 2;    // dS^T row stride (bytes)
-  static constexpr int DSB = kBKV * DSS;      // dS^T of 32 queries
-  static_assert(DSB <= 2 * RT, "dS^T must fit in a stage's Q | dO region");
-  static constexpr int KT_OFF = 2 * STAGE;
-  static constexpr int DS_OFF = KT_OFF + D * KTS;  // dS^T of the first 32 queries
-  static constexpr int BYTES = FUSED ? DS_OFF + DSB : 2 * STAGE;
+  using Rows = SwzRows<D>;
+  static constexpr int RT = Rows::bytes(kBQ);        // Q or dO rows of a tile
+  static constexpr int COPIES = kBQ / Rows::RPC;     // wave copies of each
+  static constexpr int STAGE = 2 * RT;
+  static constexpr int SQ = 256;                     // queries per copy of row statistics
+  static constexpr int SB = 2 * SQ * 4;              // -LSE/c[SQ] | -D[SQ]
+  static constexpr int ST_OFF = 2 * STAGE;           // row statistics, two buffers
+  static constexpr int KTS = (kBKV + 8) * 2;         // K^T row stride (bytes)
+  static constexpr int DSS = (kBQ + 4) * 2;          // dS^T row stride (bytes)
+  static constexpr int DSB = kBKV * DSS;             // dS^T of one tile
+  static constexpr int KT_OFF = ST_OFF + 2 * SB;
+  static constexpr int DS_OFF = KT_OFF + D * KTS;
+  static constexpr int BYTES = FUSED ? DS_OFF + 2 * DSB : KT_OFF;
   // Byte offset of the 8-byte unit u (queries 4u .. 4u+3) of dS^T row j; row of key k.
   static __device__ __forceinline__ int ds_at(int j, int u) { return j * DSS + 8 * u; }
   static __device__ __forceinline__ int ds_row(int k) { return (k & ~31) | ((k & 3) << 3) | ((k >> 2) & 7); }
@@ -122,12 +127,9 @@ struct DkdvLds {
 template <int D, bool SPATIAL, bool FUSED>
 __global__ __launch_bounds__(64 * kDkdvWaves, 1) void bwd_dkdv_kernel(DkdvArgs a) {
   using Lds = DkdvLds<D, FUSED>;
-  constexpr int RT = Lds::RT;                 // row-major Q or dO tile bytes
-  constexpr int RS = RowTile<D>::kStride;     // their row stride
-  constexpr int TT = Lds::TT;                 // transposed tile bytes
+  using Rows = SwzRows<D>;
+  constexpr int RT = Lds::RT;
   constexpr int STAGE = Lds::STAGE;
-  constexpr int RCOPIES = RowTile<D>::kCopies;
-  constexpr int TCOPIES = TT / 1024;
   __shared__ __attribute__((aligned(1024))) char smem[Lds::BYTES];
 
   const int tid = threadIdx.x;
@@ -152,10 +154,11 @@ __global__ __launch_bounds__(64 * kDkdvWaves, 1) void bwd_dkdv_kernel(DkdvArgs a
   }
   const bool tail = !SPATIAL && ti.chunk >= 0;
   const int N = a.N;
+  const int ntq = (N + kBQ - 1) / kBQ;  // query tiles
   const size_t tok = (size_t)a.H * D;
   const size_t base = (size_t)b * N * tok + (size_t)h * D;
   const size_t bh = (size_t)b * a.H + h;
-  const int npad = a.ntile * kBQ;
+  const int npad = a.ntile * kTileTok;
   // Spatial branch with split text blocks: workgroups [0, text_blocks*text_chunks) of a head
   // take (text block, chunk of its query tiles) and come first in dispatch order, the rest
   // the other key blocks in order.
@@ -170,17 +173,24 @@ __global__ __launch_bounds__(64 * kDkdvWaves, 1) void bwd_dkdv_kernel(DkdvArgs a
   // This workgroup's keys (spatial branch: text keys, or keys of one frame).
   const RowBlock rb = row_block(kb, N, a.T, SPATIAL ? a.frame_len : 0, kBKV, true);
   const bool do_dq = FUSED && kb < a.dq_blocks;  // this key block carries its share of dQ
-  const int key = rb.r0 + w * 32 + l32;  // this lane's key (accumulator column)
-  const bool key_in = key < rb.r1;
+  // This lane's key (accumulator column), formed where it is used from a lane index that the
+  // compiler must treat as new, so that no register holds it across the walk (registers are
+  // the limit there); so are the per-lane addresses of the walk's steps.
+  auto fresh_lane = [&]() {
+    int x = lane;
+    asm volatile("" : "+v"(x));
+    return x;
+  };
+  auto lane_key = [&]() { return rb.r0 + w * 32 + (fresh_lane() & 31); };
   // Partial dK of this lane's key in its chunk (dV partials follow all dK partials); formed
   // only where it is written, so that no register holds it across the main loop.
   const size_t part_stride = (size_t)a.text_chunks * a.B * a.H * a.text_blocks * kBKV * D;
-  auto part_k = [&]() {
+  auto part_k = [&](int key) {
     return a.text_part + ((((size_t)chunk * a.B + b) * a.H + h) * a.text_blocks * kBKV + key) * D;
   };
   // Joint tail: partial dK of this lane's key (dV partials follow all dK partials).
   const size_t tail_stride = (size_t)a.tail_blocks * a.tail_chunks * kBKV * D;
-  auto tail_k = [&]() {
+  auto tail_k = [&](int key) {
     return a.tail_part + (((size_t)ti.slot * a.tail_chunks + ti.chunk) * kBKV + (key - rb.r0)) * D;
   };
 
@@ -190,25 +200,19 @@ __global__ __launch_bounds__(64 * kDkdvWaves, 1) void bwd_dkdv_kernel(DkdvArgs a
   rule.tl = a.text_len ? min(max(a.text_len[b], 0), a.T) : a.T;
   rule.L = SPATIAL ? a.frame_len : 0;
   rule.km = a.key_mask ? a.key_mask + (size_t)b * N : nullptr;
-  const bool valid = key_in && rule.key_valid(key);
+  const bool valid = lane_key() < rb.r1 && rule.key_valid(lane_key());
 
   if (!__syncthreads_or(valid)) {
     // No valid key in this workgroup: its dK, dV (or partials) are zero.
-    if (tail) {
+    const int key = lane_key();
+    if (tail || split) {
       const f32x4 z = {0.0f, 0.0f, 0.0f, 0.0f};
-      float* pk = tail_k();
+      float* pk = tail ? tail_k(key) : part_k(key);
       for (int c = 0; c < D / 4; ++c) {
         *(f32x4*)(pk + 4 * c) = z;
-        *(f32x4*)(pk + tail_stride + 4 * c) = z;
+        *(f32x4*)(pk + (tail ? tail_stride : part_stride) + 4 * c) = z;
       }
-    } else if (split) {
-      const f32x4 z = {0.0f, 0.0f, 0.0f, 0.0f};
-      float* pk = part_k();
-      for (int c = 0; c < D / 4; ++c) {
-        *(f32x4*)(pk + 4 * c) = z;
-        *(f32x4*)(pk + part_stride + 4 * c) = z;
-      }
-    } else if (key_in) {
+    } else if (key < rb.r1) {
       const bf16x8 z = zero_bf16x8();
       for (int c = 0; c < D / 8; ++c) {
         *(bf16x8*)(a.dk + base + (size_t)key * tok + 8 * c) = z;
@@ -218,55 +222,91 @@ __global__ __launch_bounds__(64 * kDkdvWaves, 1) void bwd_dkdv_kernel(DkdvArgs a
     return;
   }
 
-  // Copies query tile qt into stage st. Row-major rows past N repeat row N-1; the padded
-  // LSE (+inf) makes their probabilities zero.
-  auto issue = [&](int qt, int st) {
-    VC_LDS char* sq = (VC_LDS char*)smem + st * STAGE;
-    // Spatial branch at head_dim 128: the lane index made opaque, so that the per-lane parts
-    // of the copy addresses are formed here instead of held across the walk; at 256
-    // registers they would be spilled, and the reload's wait, at the head of this loop,
-    // would make every copy wait for the previous one.
-    int cl = lane;
-    if constexpr (SPATIAL && D == 128) asm volatile("" : "+v"(cl));
-    for (int idx = w; idx < RCOPIES; idx += kDkdvWaves) {
-      copy_row_tile<D, true, FUSED>(a.q + base, tok, qt * kBQ, N, sq, idx, cl);  // fused: perm_row order
-      copy_row_tile<D, true, FUSED>(a.dout + base, tok, qt * kBQ, N, sq + RT, idx, cl);
-    }
-    if constexpr (!FUSED) {
-      const size_t toff = (bh * a.ntile + qt) * tile_elems(D);
-      for (int idx = w; idx < TCOPIES; idx += kDkdvWaves) {
-        copy16_to_lds_opaque(a.qt + toff + idx * 512 + cl * 8, sq + 2 * RT + idx * 1024);
-        copy16_to_lds_opaque(a.dot + toff + idx * 512 + cl * 8, sq + 2 * RT + TT + idx * 1024);
-      }
-    }
-    // LSE*log2e by lanes 0-15, -D by lanes 16-31 of the last wave. Spatial branch: two
-    // copies from uniform bases, so that no per-lane pointer is held across the walk.
-    if constexpr (SPATIAL) {
-      if (w == kDkdvWaves - 1) {
-        const size_t r0 = bh * npad + qt * kBQ;
-        if (cl < 16)
-          copy16_to_lds_opaque(a.lse2 + r0 + 4 * cl, sq + 2 * RT + 2 * TT);
-        else if (cl < 32)
-          copy16_to_lds_opaque(a.dd + r0 + 4 * (cl - 16), sq + 2 * RT + 2 * TT);
-      }
-    } else if (w == kDkdvWaves - 1 && lane < 32) {
-      const float* src = (lane < 16 ? a.lse2 : a.dd) + bh * npad + qt * kBQ + 4 * (lane & 15);
-      copy16_to_lds_opaque(src, sq + 2 * RT + 2 * TT);
-    }
+  // This wave's copies of query tile qt into stage st: j = 0 Q rows, j = 1 dO rows (at
+  // head_dim 64 each wave has one of the two). Rows past N repeat row N-1; the padded -LSE
+  // (-inf) makes their probabilities zero. The lane index is made opaque, so that the lane's
+  // part of the addresses is formed once per tile instead of being held across the walk.
+  static_assert(Lds::COPIES == (D == 128 ? kDkdvWaves : kDkdvWaves / 2), "copies of a tile over the waves");
+  struct TileCopy {
+    int first;
+    unsigned off;
   };
+  auto tile_copy = [&](int qt) {
+    unsigned cl = lane;
+    asm volatile("" : "+v"(cl));
+    const int first = swz_copy_row<D, true>(qt * kBQ, N, w % Lds::COPIES);
+    return TileCopy{first, swz_copy_off<D, true>(first, (unsigned)tok, N, cl)};
+  };
+  auto issue_j = [&](int j, const TileCopy& tc, int st) {
+    if (D == 64 && j == 1) return;
+    const bool is_q = D == 128 ? j == 0 : w < Lds::COPIES;
+    copy16_to_lds_opaque((is_q ? a.q : a.dout) + base + (size_t)tc.first * tok, tc.off,
+                         (VC_LDS char*)smem + st * STAGE + (is_q ? 0 : RT) + (w % Lds::COPIES) * Rows::GS);
+  };
+  // Query tiles this workgroup visits (the same sequence for every wave): all of them in
+  // joint attention; in the spatial branch the video tiles its keys are attended from. The
+  // host's spans count tiles of kTileTok queries.
+  constexpr int TPS = kTileTok / kBQ;
+  TileRuns runs = rule.query_tiles(rb.r0, rb.r1, ntq, kBQ);
+  if (split) {  // this chunk's part of the video query tiles
+    const int c0 = (a.T / kTileTok + chunk * a.text_span) * TPS;
+    runs.b0 = max(runs.b0, c0);
+    runs.b1 = min(runs.b1, c0 + a.text_span * TPS);
+    if (runs.b0 >= runs.b1) runs.b1 = 0;
+  }
+  if (tail) {  // this chunk's run of query tiles
+    runs.b0 = ti.chunk * a.tail_span * TPS;
+    runs.b1 = min(ntq, runs.b0 + a.tail_span * TPS);
+    if (runs.b0 >= runs.b1) runs.b1 = 0;
+  }
+  auto next_q = [&](int qt) { return (SPATIAL || tail) ? runs.next(qt) : qt; };
+  // Spatial branch: the queries attending to this workgroup's keys, [kx, ky) (its keys are all
+  // text, attended from every video row, or all of one frame); a tile needs the per-query
+  // test unless it lies inside.
+  const bool text_keys = SPATIAL && rb.r0 < a.T;
+  const int kx = SPATIAL ? (text_keys ? a.T : rule.frame_start(rb.r0)) : 0;
+  const int ky = text_keys ? N : kx + rule.L;
 
+  // dQ: the workgroups of each XCD (dispatch is round-robin over the XCDs) start
+  // their walk over the query tiles at a different eighth of them, so that the atomics
+  // of concurrent workgroups land on different rows of the accumulator. Walk position u
+  // visits tile phys(u).
+  const int xs = (FUSED && !SPATIAL && !tail) ? (int)((blockIdx.x % kXcds) * ((ntq + kXcds - 1) / kXcds)) % ntq : 0;
+  auto phys = [&](int u) { return u + xs >= ntq ? u + xs - ntq : u + xs; };
+  // The statistics of the SQ / kBQ walk positions around u (the aligned run holding it) into
+  // their buffer, by the last two waves (past the padded length: its last four repeated).
+  constexpr int SPT = Lds::SQ / kBQ;
+  auto issue_stats = [&](int u) {
+    if (w < kDkdvWaves - 2) return;
+    int cl = lane;
+    asm volatile("" : "+v"(cl));
+    const bool is_l = w == kDkdvWaves - 2;
+    int q = ((u & -SPT) + xs) * kBQ + 4 * cl;
+    q = q >= ntq * kBQ ? q - ntq * kBQ : q;  // the walk wraps past the last tile
+    copy16_to_lds_opaque((is_l ? a.nls : a.dd) + bh * npad, 4u * (unsigned)min(q, npad - 4),
+                         (VC_LDS char*)smem + Lds::ST_OFF + (u / SPT % 2) * Lds::SB + (is_l ? 0 : Lds::SQ * 4));
+  };
+  // The first tile's copies, in flight with the loads of K and V.
+  const int qt0 = next_q(0);
+  if (qt0 < ntq) {
+    const TileCopy tc = tile_copy(phys(qt0));
+    issue_stats(qt0);
+    issue_j(0, tc, 0);
+    issue_j(1, tc, 0);
+  }
   // K, V of this lane's key as B operands (dims 16*ks + 8*hi .. +7).
   bf16x8 kf[D / 16], vf[D / 16];
   {
-    const size_t kr = base + (size_t)min(key, rb.r1 - 1) * tok + 8 * hi;
+    const size_t kr = base + (size_t)min(lane_key(), rb.r1 - 1) * tok + 8 * hi;
 #pragma unroll
     for (int ks = 0; ks < D / 16; ++ks) {
       kf[ks] = *(const bf16x8*)(a.k + kr + 16 * ks);
       vf[ks] = *(const bf16x8*)(a.v + kr + 16 * ks);
     }
+    wait_all_memory();  // and the first tile's copies: no later wait stands among copies
   }
 
-  // Fused dQ: K^T of the workgroup's keys (row d holds K[key][d] of its 256 keys).
+  // dQ: K^T of the workgroup's keys (row d holds K[key][d] of its 256 keys).
   if (FUSED && do_dq) {
     VC_LDS __bf16* ktl = (VC_LDS __bf16*)(smem + Lds::KT_OFF);
     const int kl = w * 32 + l32;
@@ -283,248 +323,268 @@ __global__ __launch_bounds__(64 * kDkdvWaves, 1) void bwd_dkdv_kernel(DkdvArgs a
     dv_acc[i] = zero_f32x16();
   }
 
-  // Query tiles this workgroup visits (the same sequence for every wave): all of them in
-  // joint attention; in the spatial branch the video tiles its keys are attended from.
-  TileRuns runs = rule.query_tiles(rb.r0, rb.r1, a.ntile);
-  if (split) {  // this chunk's part of the video query tiles
-    const int c0 = a.T / kBQ + chunk * a.text_span;
-    runs.b0 = max(runs.b0, c0);
-    runs.b1 = min(runs.b1, c0 + a.text_span);
-    if (runs.b0 >= runs.b1) runs.b1 = 0;
-  }
-  if (tail) {  // this chunk's run of query tiles
-    runs.b0 = ti.chunk * a.tail_span;
-    runs.b1 = min(a.ntile, runs.b0 + a.tail_span);
-    if (runs.b0 >= runs.b1) runs.b1 = 0;
-  }
-  auto next_q = [&](int qt) { return (SPATIAL || tail) ? runs.next(qt) : qt; };
-  // Spatial branch: a tile needs the per-pair test unless this wave's keys are all text
-  // and the tile holds video queries only, or they all lie in one frame containing it.
-  // (a wave past the end of a short block takes its last row)
-  const int kw0 = min(rb.r0 + w * 32, rb.r1 - 1), kw1 = min(rb.r0 + w * 32 + 31, rb.r1 - 1);
-  const bool wave_text_keys = kw1 < a.T;
-  const int wks = SPATIAL ? rule.frame_start(kw0) : 0;
-  const bool wave_one_frame = SPATIAL && kw0 >= a.T && kw1 < N && rule.frame_start(kw1) == wks;
-  const int2 kr = key_range(rule, key);  // spatial: queries attending to this lane's key
-
-  // Fused dQ: the workgroups of each XCD (dispatch is round-robin over the XCDs) start
-  // their walk over the query tiles at a different eighth of them, so that the atomics
-  // of concurrent workgroups land on different rows of the accumulator. Walk position u
-  // visits tile phys(u).
-  const int xs = (FUSED && !SPATIAL && !tail) ? (int)((blockIdx.x % kXcds) * ((a.ntile + kXcds - 1) / kXcds)) % a.ntile : 0;
-  auto phys = [&](int u) { return u + xs >= a.ntile ? u + xs - a.ntile : u + xs; };
-  // Fused dQ: wave w < DQ_BLOCKS forms the 32x32 block (query block dq_qb, dim block dq_db)
-  // of the tile's dQ over the workgroup's 256 keys. With fewer blocks than waves (head_dim
-  // 64: four), waves 0..3 take them, one per SIMD (wave w shares its SIMD with wave w + 4),
-  // so that each element still gets one atomic addition per key block.
-  constexpr int DQ_BLOCKS = 2 * (D / 32);
+  // A tile's dQ has D/32 blocks of 32 queries x 32 dims. The waves form them in turns, D/32
+  // waves per tile (of different SIMDs: wave w shares its SIMD with wave w + 4): group
+  // w / (D/32) takes every DQ_TURNS-th tile, wave w of it the dims 32*(w % (D/32)). While one
+  // of a SIMD's two waves forms its dQ block of the previous tile, the other is already in
+  // this tile's products, so the two run out of step and one's vector arithmetic overlaps
+  // the other's matrix-core work; with every wave taking a block of every tile they ran in
+  // step from barrier to barrier.
+  constexpr int NB = D / 32;
   constexpr int DQ_STEPS = kBKV / 16;
-  static_assert(DQ_BLOCKS == kDkdvWaves || DQ_BLOCKS == kDkdvWaves / 2, "dQ blocks per wave");
-  const bool dq_wave = DQ_BLOCKS == kDkdvWaves || w < DQ_BLOCKS;  // constant for head_dim 128
-  const int dq_qb = w & 1, dq_db = (w >> 1) % (D / 32);
-  f32x16 dq_blk;
-  int dq_row0 = -1;  // first query row of the block awaiting its atomics, -1: none
-  // The lane index as a value the compiler must treat as new at each use: per-lane
-  // addresses of the fused steps derived from it are formed where they are used instead
-  // of being kept in registers across the whole loop (registers are the limit here).
-  auto fresh_lane = [&]() {
-    int x = lane;
-    asm volatile("" : "+v"(x));
-    return x;
+  constexpr int DQ_TURNS = kDkdvWaves / NB;
+  const int dq_turn = w / NB, dq_db = w % NB;
+  // Operand reads from a tile's swizzled rows, as one per-lane base each that a fixed XOR
+  // (formed where it is used, so that no further register is held) turns into the others:
+  // Plain reads of the A operands Q, dO: the lane's query row, chunk 2*ks + hi.
+  const int row_base = Rows::off(perm_row(l32), hi);
+  auto row_at = [](const VC_LDS char* p, int ks) {  // p = tile + row_base
+    return (const VC_LDS char*)((unsigned)(size_t)p ^ (32u * (ks % Rows::NBASE))) + ks / Rows::NBASE * 64;
   };
-  // Adds the pending dQ block to the accumulator (rows past N are padding): a uniform base
-  // plus a 32-bit per-lane offset (the host launches the fused pass only when a sample's
-  // N*H*D elements fit in 32 bits).
-  float* const dq_dst = FUSED ? a.dq_acc + (size_t)b * N * tok + (size_t)h * D + dq_db * 32 : nullptr;
-  auto flush_dq = [&]() {
-    if (dq_row0 < 0) return;
+  // Transposing reads of the A operands Q^T, dO^T (rows in perm_row order): lane l of 16-lane
+  // group G supplies query 16*st2 + 8*part + 4*hi + (l%16)/4 and dims 32*db + 16*(G%2) +
+  // 4*(l%4) .. +3. Part 1 lies two LDS rows on, its chunks' swizzle differing by 2.
+  constexpr int TGS = 16 / Rows::RPC * Rows::GS;  // bytes between k-steps (16 rows)
+  const int tr_base =
+      Rows::off(perm_row(4 * hi + ((lane & 15) >> 2)), 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) + 8 * (lane & 1);
+  auto tr_at = [](const VC_LDS char* p, int st2, int db, int part) {  // p = tile + tr_base
+    const unsigned x = (D == 64 ? 64u * db : 0u) ^ (32u * part);
+    return (const VC_LDS char*)((unsigned)(size_t)p ^ x) + st2 * TGS + part * 4 * D + (D == 64 ? 0 : 64 * db);
+  };
+
+  // dQ block of the tile starting at query row0, whose dS^T is in buffer `buf`: A = dS
+  // (queries x keys) by transposing reads of dS^T, B = K from K^T. Lane l of 16-lane group G
+  // supplies key 16*st + 8*hi + (l%16)/4 (+4), i.e. row 32*(st/2) + 4*(st%2) + 8*((l%16)/4) +
+  // 2*hi (+1), and unit 4*(G%2) + l%4 of that row. The block is added to the accumulator with
+  // a uniform base plus a 32-bit per-lane offset (the host fuses dQ only when a sample's
+  // N*H*D elements fit in 32 bits); rows past N are padding.
+  auto dq_step = [&](int row0, int buf) {
     const int ln = fresh_lane();
-    const int col = ln & 31, half = ln >> 5;
+    const VC_LDS char* ds_src = (const VC_LDS char*)smem + Lds::DS_OFF + buf * Lds::DSB;
+    const int arow = 8 * ((ln & 15) >> 2) + 2 * (ln >> 5), aunit = 4 * ((ln >> 4) & 1) + (ln & 3);
+    const VC_LDS char* b_base =
+        (const VC_LDS char*)smem + Lds::KT_OFF + (dq_db * 32 + (ln & 31)) * Lds::KTS + 8 * (ln >> 5) * 2;
+    f32x16 blk = zero_f32x16();
+    constexpr int PF = 4;  // operands read this many ops ahead
+    bf16x8 da[DQ_STEPS], kb8[DQ_STEPS];
+    auto rd = [&](int st) {
+      const int j = arow + 32 * (st >> 1) + 4 * (st & 1);
+      da[st] = cat4(lds_read_tr(ds_src + Lds::ds_at(j, aunit)), lds_read_tr(ds_src + Lds::ds_at(j + 1, aunit)));
+      kb8[st] = *(const VC_LDS bf16x8*)(b_base + st * 32);
+    };
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int qrow = dq_row0 + acc_row(r, half);
-      if (qrow < N) atomicAdd(dq_dst + ((unsigned)qrow * (unsigned)tok + (unsigned)col), dq_blk[r]);
+    for (int st = 0; st < PF; ++st) rd(st);
+#pragma unroll
+    for (int st = 0; st < DQ_STEPS; ++st) {
+      sched_fence();
+      if (st + PF < DQ_STEPS) rd(st + PF);
+      blk = mfma32(da[st], kb8[st], blk);
     }
-    dq_row0 = -1;
+    sched_fence();
+    // Register r of lane (col, half): query row0 + 8*(r/4) + r%4 + 4*half, dim dq_db*32 + col.
+    float* const dst = a.dq_acc + (size_t)b * N * tok + (size_t)h * D + dq_db * 32 + (size_t)row0 * tok;
+    const int ln2 = fresh_lane();
+    const int half = ln2 >> 5;
+    const unsigned loff = (unsigned)(4 * half) * (unsigned)tok + (unsigned)(ln2 & 31);
+    if (row0 + kBQ <= N) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) atomicAdd(dst + (size_t)(8 * (r >> 2) + (r & 3)) * tok + loff, blk[r]);
+    } else {
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        if (row0 + acc_row(r, half) < N) atomicAdd(dst + (size_t)(8 * (r >> 2) + (r & 3)) * tok + loff, blk[r]);
+    }
   };
-  // Transposing reads of the A operands Q^T, dO^T from the row-major tiles (fused: rows in
-  // perm_row order): lane l of 16-lane group G supplies query 4*hi + (l%16)/4, i.e. row
-  // 4*((l%16)/4) + hi, and column 16*(G%2) + 4*(l%4), relative to the operand's first query
-  // row and dim block; the operand's other four queries (+8) lie 2 rows further.
-  const int tr_base = (4 * ((lane & 15) >> 2) + hi) * RS + (16 * ((lane >> 4) & 1) + 4 * (lane & 3)) * 2;
-  // Row of this lane's query in the plain operand reads (fused: perm_row order).
-  const int prow = FUSED ? perm_row(l32) : l32;
-  VC_LDS char* ds_own = (VC_LDS char*)smem + Lds::DS_OFF;
 
   // The walk over the query tiles; DQ: this workgroup also adds its dQ share (a separate
-  // instance of the loop, so that neither carries the other's registers).
+  // instance of the loop, so that neither carries the other's registers). One barrier per
+  // tile: past it, stage st holds the tile, dS^T of the previous tile is complete, and no
+  // wave reads the other stage or the other dS^T buffer.
   auto walk = [&](auto dq_tag) {
-    constexpr bool DQ = FUSED && decltype(dq_tag)::value;
-    int qt = next_q(0);
-    if (qt < a.ntile) issue(phys(qt), 0);
-    for (int st = 0; qt < a.ntile; st ^= 1) {  // stage st holds tile qt, stage st ^ 1 the next
+    constexpr bool DQ = decltype(dq_tag)::value;
+    int qt = qt0;
+    int prev0 = -1;  // first query row of the previous tile, -1: none
+    int turn = 0;    // whose turn the previous tile's dQ is
+    for (int st = 0; qt < ntq; st ^= 1) {  // stage st holds tile qt, stage st ^ 1 takes the next
       const int qn = next_q(qt + 1);
       wait_all_memory();
-      __syncthreads();  // stage st holds tile qt; every wave is done with the other stage
+      __syncthreads();
       if constexpr (DQ) {
-        flush_dq();     // the previous tile's dQ block; waited for at the next tile
-        sched_fence();  // its registers are free before the copies and products begin
+        if (prev0 >= 0) {
+          if (turn == dq_turn) dq_step(prev0, st ^ 1);
+          turn = (turn + 1) % DQ_TURNS;
+        }
+        sched_fence();
       }
-      if (qn < a.ntile) issue(phys(qn), st ^ 1);
       const int q0 = phys(qt) * kBQ;
-      const bool pair_mask = SPATIAL && !((wave_text_keys && q0 >= a.T) ||
-                                          (wave_one_frame && q0 >= wks && q0 + kBQ <= wks + rule.L));
-      VC_LDS char* stage = (VC_LDS char*)smem + st * STAGE;
-      const VC_LDS char* q_lds = stage;
-      const VC_LDS char* do_lds = q_lds + RT;
-      const VC_LDS char* qt_lds = q_lds + 2 * RT;
-      const VC_LDS char* dot_lds = qt_lds + TT;
-      const VC_LDS float* lse_lds = (const VC_LDS float*)(qt_lds + 2 * TT);
-      const VC_LDS float* dd_lds = lse_lds + kBQ;
-      bf16x8 ds_keep[2];  // fused: dS of the second query block as bf16 operands, for dQ
+      const TileCopy tc = tile_copy(phys(qn < ntq ? qn : qt));  // past the last tile: any tile, never read
+      if (qn % SPT == 0 && qn < ntq) issue_stats(qn);
+      const bool pair_mask = SPATIAL && !(q0 >= kx && q0 + kBQ <= ky);
+      const VC_LDS char* q_lds = (const VC_LDS char*)smem + st * STAGE;
+      const VC_LDS float* nls_lds =
+          (const VC_LDS float*)((const VC_LDS char*)smem + Lds::ST_OFF + (qt / SPT % 2) * Lds::SB) + qt % SPT * kBQ + 4 * (fresh_lane() >> 5);
+      const VC_LDS float* dd_lds = nls_lds + Lds::SQ;
 
-      auto query_block = [&](int qb) {
-        f32x16 s = zero_f32x16(), dp;
-  #pragma unroll
-        for (int j = 0; j < 4; ++j) {  // dP accumulates on top of -D of its query rows
-          const f32x4 nd = *(const VC_LDS f32x4*)(dd_lds + qb * 32 + 8 * j + 4 * hi);
-  #pragma unroll
-          for (int i = 0; i < 4; ++i) dp[4 * j + i] = nd[i];
-        }
-  #pragma unroll
-        for (int ks = 0; ks < D / 16; ++ks) {
-          const bf16x8 qa = *(const VC_LDS bf16x8*)(q_lds + (qb * 32 + prow) * RS + (2 * ks + hi) * 16);
-          s = mfma32(qa, kf[ks], s);
-        }
-  #pragma unroll
-        for (int ks = 0; ks < D / 16; ++ks) {
-          const bf16x8 da = *(const VC_LDS bf16x8*)(do_lds + (qb * 32 + prow) * RS + (2 * ks + hi) * 16);
-          dp = mfma32(da, vf[ks], dp);
-        }
-        // Register r holds query row qb*32 + 8*(r/4) + 4*hi + r%4: four runs of 4 rows.
-        // Spatial branch: on tiles needing the per-pair test, queries outside [kr.x, kr.y)
-        // (this lane's key range) get probability zero.
-        const int row0 = pair_mask ? q0 + qb * 32 : kr.x;
-        float p[16], ds[16];
-  #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const f32x4 l2 = *(const VC_LDS f32x4*)(lse_lds + qb * 32 + 8 * j + 4 * hi);
-  #pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const int r = 4 * j + i;
-            p[r] = fast_exp2(fmaf(s[r], a.scale_log2, -l2[i]));
-            if (SPATIAL) {
-              const int qrow = row0 + acc_row(r, hi);
-              p[r] = (valid & (!pair_mask | ((qrow >= kr.x) & (qrow < kr.y)))) ? p[r] : 0.0f;
-            }
-            // Joint attention needs no test for dK, dV: the probabilities of an invalid key
-            // reach only its own lane's dK, dV, which are written as zero at the end. Its dS
-            // also reaches dQ, so with dQ fused it is zeroed (its P may even be inf).
-            ds[r] = p[r] * dp[r];
-            if (DQ) ds[r] = valid ? ds[r] : 0.0f;
-          }
-        }
-        // Operand element t of k-step st2 is query 16*st2 + 8*(t/4) + 4*hi + t%4: stored by
-        // the transposed tiles as 8 consecutive elements at position 16*st2 + 8*hi, or read
-        // from the row-major tiles by two transposing reads (rows +0..3 and +8..11).
-        // Operands of the 2 * D/32 products in order (k-step st2 major, dim block db minor),
-        // each read one product ahead: the read is in flight while the previous pair runs.
-        constexpr int NB = D / 32;
-        const int obase = (l32 * kTileRow + qb * 32 + 8 * hi) * 2;
-        auto opnd = [&](int idx, const VC_LDS char* bp) {
-          if constexpr (FUSED) {
-            const VC_LDS char* p0 = bp + tr_base + (qb * 32 + 16 * (idx / NB)) * RS + (idx % NB) * 64;
-            return cat4(lds_read_tr(p0), lds_read_tr(p0 + 2 * RS));
-          } else {
-            return *(const VC_LDS bf16x8*)(bp + obase + ((idx % NB) * 32 * kTileRow + 16 * (idx / NB)) * 2);
-          }
-        };
-        if constexpr (DQ) {
-          // dS^T of this query block: element t of operand st2 is query 16*st2 + 8*(t/4) +
-          // 4*hi + t%4, i.e. units 4*st2 + hi and 4*st2 + 2 + hi. Block 0 goes to its own
-          // region now; block 1 waits until the stage's Q and dO are no longer read.
-          if (qb == 0) {
-            const int ln = fresh_lane();
-            const int kl = Lds::ds_row(w * 32 + (ln & 31)), hl = ln >> 5;  // dS^T row, lane half
-  #pragma unroll
-            for (int st2 = 0; st2 < 2; ++st2) {
-              const bf16x8 x = to_bf16x8(&ds[8 * st2]);
-              *(VC_LDS bf16x4*)(ds_own + Lds::ds_at(kl, 4 * st2 + hl)) = bf16x4{x[0], x[1], x[2], x[3]};
-              *(VC_LDS bf16x4*)(ds_own + Lds::ds_at(kl, 4 * st2 + 2 + hl)) = bf16x4{x[4], x[5], x[6], x[7]};
-            }
-          }
-        }
-        const VC_LDS char* v_src = FUSED ? do_lds : dot_lds;
-        const VC_LDS char* k_src = FUSED ? q_lds : qt_lds;
-        bf16x8 av = opnd(0, v_src), ak = opnd(0, k_src);
-  #pragma unroll
-        for (int st2 = 0; st2 < 2; ++st2) {
-          const bf16x8 pb = to_bf16x8(&p[8 * st2]);
-          const bf16x8 sb = to_bf16x8(&ds[8 * st2]);
-          if constexpr (DQ) ds_keep[st2] = sb;
-  #pragma unroll
-          for (int db = 0; db < NB; ++db) {
-            const int nx = st2 * NB + db + 1;
-            bf16x8 vn = av, kn = ak;
-            if (nx < 2 * NB) {
-              vn = opnd(nx, v_src);
-              kn = opnd(nx, k_src);
-            }
-            dv_acc[db] = mfma32(av, pb, dv_acc[db]);
-            dk_acc[db] = mfma32(ak, sb, dk_acc[db]);
-            av = vn;
-            ak = kn;
-          }
-        }
+      // The tile's products in one stretch of 4 * KSN matrix-core ops, every LDS operand read
+      // PF ops ahead of its use, each phase's vector arithmetic placed between the ops of the
+      // next one (which do not depend on it): S = Q K^T; dP = -D + dO V^T while P is formed;
+      // dV^T += dO^T P while dS is formed; dK^T += Q^T dS. Left to the compiler, the reads
+      // came two ops ahead at most and the arithmetic stood between the products.
+      constexpr int KSN = D / 16;
+      constexpr int PF = 2;
+      constexpr int EP = 16 / KSN;       // elements of P per dP op
+      constexpr int ED = 16 / (2 * NB);  // elements of dS per dV op
+      f32x16 s, dp;
+      bf16x8 f[2 * KSN];
+      auto rd = [&](int i) {
+        f[i] = *(const VC_LDS bf16x8*)(row_at(q_lds + row_base, i % KSN) + (i < KSN ? 0 : RT));
       };
-  #pragma unroll 1
-      for (int qb = 0; qb < kBQ / 32; ++qb) query_block(qb);
-
-      if constexpr (DQ) {
-        __syncthreads();  // every wave is done reading this stage's Q and dO
-        const int ln = fresh_lane();
-        {
-          const int kl = Lds::ds_row(w * 32 + (ln & 31)), hl = ln >> 5;
-  #pragma unroll
-          for (int st2 = 0; st2 < 2; ++st2) {
-            const bf16x8 x = ds_keep[st2];
-            *(VC_LDS bf16x4*)(stage + Lds::ds_at(kl, 4 * st2 + hl)) = bf16x4{x[0], x[1], x[2], x[3]};
-            *(VC_LDS bf16x4*)(stage + Lds::ds_at(kl, 4 * st2 + 2 + hl)) = bf16x4{x[4], x[5], x[6], x[7]};
-          }
+      // Operand element t of k-step st2 is query 16*st2 + 8*(t/4) + 4*hi + t%4, read from the
+      // row-major tiles by two transposing reads (queries +0..3 and +8..11). Operand i: dO^T,
+      // then Q^T, k-step st2 = (i / NB) % 2 major, dim block i % NB minor.
+      bf16x8 g[4 * NB];
+      auto rdt = [&](int i) {
+        const int o = i < 2 * NB ? RT : 0;
+        g[i] = cat4(lds_read_tr(tr_at(q_lds + tr_base, i / NB % 2, i % NB, 0) + o),
+                    lds_read_tr(tr_at(q_lds + tr_base, i / NB % 2, i % NB, 1) + o));
+      };
+      // Register r holds query row 8*(r/4) + 4*hi + r%4 of the tile: four runs of 4 rows.
+      auto form_p = [&](int r) {
+        s[r] = fast_exp2(s[r] * a.scale_log2);
+      };
+      auto operand = [&](const f32x16& x, int half) {
+        bf16x8 y;
+#pragma unroll
+        for (int t = 0; t < 8; ++t) y[t] = (__bf16)x[8 * half + t];
+        return y;
+      };
+      auto form_ds = [&](int r) { dp[r] = s[r] * dp[r]; };
+      // dS as operand `half`. An invalid key needs no test for dK, dV: its probabilities
+      // reach only its own lane's dK, dV, which are written as zero at the end.
+      // Its dS also reaches dQ, so with dQ formed here it is zeroed (its P may even be inf).
+      auto ds_operand = [&](int half) {
+        typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+        u32x4 y = __builtin_bit_cast(u32x4, operand(dp, half));
+        if (DQ) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) y[e] = valid ? y[e] : 0u;
         }
-        __syncthreads();  // dS^T of both query blocks complete
-        if (dq_wave) {
-          // dQ block: A = dS (queries x keys) by transposing reads of dS^T (this wave's query
-          // block's region), B = K from K^T. Lane l of 16-lane group G supplies key
-          // 16*st + 8*hi + (l%16)/4 (+4), i.e. row 32*(st/2) + 4*(st%2) + 8*((l%16)/4) + 2*hi
-          // (+1), and unit 4*(G%2) + l%4 of that row.
-          const VC_LDS char* ds_src = dq_qb ? (const VC_LDS char*)stage : (const VC_LDS char*)ds_own;
-          const int arow = 8 * ((ln & 15) >> 2) + 2 * (ln >> 5), aunit = 4 * ((ln >> 4) & 1) + (ln & 3);
-          const VC_LDS char* b_base =
-              (const VC_LDS char*)smem + Lds::KT_OFF + (dq_db * 32 + (ln & 31)) * Lds::KTS + 8 * (ln >> 5) * 2;
-          dq_blk = zero_f32x16();
-  #pragma unroll
-          for (int st = 0; st < DQ_STEPS; ++st) {
-            const int j = arow + 32 * (st >> 1) + 4 * (st & 1);
-            const bf16x8 da = cat4(lds_read_tr(ds_src + Lds::ds_at(j, aunit)), lds_read_tr(ds_src + Lds::ds_at(j + 1, aunit)));
-            const bf16x8 kb8 = *(const VC_LDS bf16x8*)(b_base + st * 32);
-            dq_blk = mfma32(da, kb8, dq_blk);
-          }
-          dq_row0 = q0 + dq_qb * 32;
+        return __builtin_bit_cast(bf16x8, y);
+      };
+#pragma unroll
+      for (int i = 0; i < PF; ++i) rd(i);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {  // S accumulates on top of -LSE/c, dP on top of -D of its query rows
+        const f32x4 nl = *(const VC_LDS f32x4*)(nls_lds + 8 * j), nd = *(const VC_LDS f32x4*)(dd_lds + 8 * j);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          s[4 * j + i] = nl[i];
+          dp[4 * j + i] = nd[i];
         }
       }
+#pragma unroll
+      for (int i = 0; i < KSN; ++i) {
+        sched_fence();
+        rd(i + PF);
+        s = mfma32(f[i], kf[i], s);
+        // The next tile's copies, one at a time: issued together at the top of the step, eight
+        // waves' copies would hold up the start of every wave's products.
+        if (i == 0 || i == 2) issue_j(i / 2, tc, st ^ 1);
+      }
+      if (SPATIAL && pair_mask) {  // queries outside [kx, ky) get probability zero
+        sched_fence();
+        const int half = fresh_lane() >> 5;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int qrow = q0 + acc_row(r, half);
+          s[r] = (qrow >= kx) & (qrow < ky) ? s[r] : -INFINITY;
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < KSN; ++i) {
+        sched_fence();
+        if (i + PF < KSN)
+          rd(KSN + i + PF);
+        else
+          rdt(i + PF - KSN);
+        dp = mfma32(f[KSN + i], vf[i], dp);
+        if (i > 0) {
+#pragma unroll
+          for (int e = 0; e < EP; ++e) form_p((i - 1) * EP + e);
+        }
+      }
+      bf16x8 pb[2], sb[2];
+      sched_fence();
+      pb[0] = operand(s, 0);
+#pragma unroll
+      for (int i = 0; i < 2 * NB; ++i) {
+        sched_fence();
+        rdt(i + PF);
+        dv_acc[i % NB] = mfma32(g[i], pb[i / NB], dv_acc[i % NB]);
+        if (i == 0) {
+#pragma unroll
+          for (int e = 0; e < EP; ++e) form_p((KSN - 1) * EP + e);
+          pb[1] = operand(s, 1);
+        } else {
+#pragma unroll
+          for (int e = 0; e < ED; ++e) form_ds((i - 1) * ED + e);
+        }
+      }
+      sched_fence();
+      sb[0] = ds_operand(0);
+#pragma unroll
+      for (int i = 0; i < 2 * NB; ++i) {
+        sched_fence();
+        if (2 * NB + i + PF < 4 * NB) rdt(2 * NB + i + PF);
+        dk_acc[i % NB] = mfma32(g[2 * NB + i], sb[i / NB], dk_acc[i % NB]);
+        if (i == 0) {
+#pragma unroll
+          for (int e = 0; e < ED; ++e) form_ds((2 * NB - 1) * ED + e);
+          sb[1] = ds_operand(1);
+        }
+        if (i == 1) {
+          if constexpr (DQ) {
+            // dS^T: element t of operand st2 is query 16*st2 + 8*(t/4) + 4*hi + t%4, i.e. units
+            // 4*st2 + hi and 4*st2 + 2 + hi.
+            const int ln = fresh_lane();
+            VC_LDS char* ds_dst = (VC_LDS char*)smem + Lds::DS_OFF + st * Lds::DSB;
+            const int kl = Lds::ds_row(w * 32 + (ln & 31)), hl = ln >> 5;  // dS^T row, lane half
+#pragma unroll
+            for (int st2 = 0; st2 < 2; ++st2) {
+              const bf16x8 x = sb[st2];
+              *(VC_LDS bf16x4*)(ds_dst + Lds::ds_at(kl, 4 * st2 + hl)) = bf16x4{x[0], x[1], x[2], x[3]};
+              *(VC_LDS bf16x4*)(ds_dst + Lds::ds_at(kl, 4 * st2 + 2 + hl)) = bf16x4{x[4], x[5], x[6], x[7]};
+            }
+          }
+        }
+      }
+      sched_fence();
+      if constexpr (DQ) prev0 = q0;
       qt = qn;
+      if constexpr (DQ) {
+        if (qn >= ntq) {  // the last tile's dQ
+          __syncthreads();
+          if (turn == dq_turn) dq_step(prev0, st);
+        }
+      }
     }
-    if constexpr (DQ) flush_dq();
   };
-  if (do_dq)
-    walk(std::true_type{});
-  else
+  if constexpr (FUSED) {
+    if (do_dq)
+      walk(std::true_type{});
+    else
+      walk(std::false_type{});
+  } else {
     walk(std::false_type{});
+  }
 
-  if (tail) {
-    // An invalid key's partials are zero (its accumulators may hold anything).
-    float* pk = tail_k();
+  wait_all_memory();  // no copy outlives the workgroup
+  const int key = lane_key();
+
+  if (tail || split) {
+    // fp32 partials; an invalid key's are zero (its accumulators may hold anything).
+    float* pk = tail ? tail_k(key) : part_k(key);
+    float* pv = pk + (tail ? tail_stride : part_stride);
 #pragma unroll
     for (int db = 0; db < D / 32; ++db)
 #pragma unroll
@@ -536,21 +596,9 @@ __global__ __launch_bounds__(64 * kDkdvWaves, 1) void bwd_dkdv_kernel(DkdvArgs a
           tv[e] = valid ? dv_acc[db][4 * j + e] : 0.0f;
         }
         *(f32x4*)(pk + db * 32 + 8 * j + 4 * hi) = tk;
-        *(f32x4*)(pk + tail_stride + db * 32 + 8 * j + 4 * hi) = tv;
+        *(f32x4*)(pv + db * 32 + 8 * j + 4 * hi) = tv;
       }
-  } else if (split) {
-    float* pk = part_k();
-#pragma unroll
-    for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const f32x4 tk = {dk_acc[db][4 * j + 0] * a.scale, dk_acc[db][4 * j + 1] * a.scale,
-                          dk_acc[db][4 * j + 2] * a.scale, dk_acc[db][4 * j + 3] * a.scale};
-        const f32x4 tv = {dv_acc[db][4 * j + 0], dv_acc[db][4 * j + 1], dv_acc[db][4 * j + 2], dv_acc[db][4 * j + 3]};
-        *(f32x4*)(pk + db * 32 + 8 * j + 4 * hi) = tk;
-        *(f32x4*)(pk + part_stride + db * 32 + 8 * j + 4 * hi) = tv;
-      }
-  } else if (key_in) {
+  } else if (key < rb.r1) {
     __bf16* dkp = a.dk + base + (size_t)key * tok;
     __bf16* dvp = a.dv + base + (size_t)key * tok;
     // An invalid key gets exactly zero (its accumulators may hold anything, even inf).
@@ -673,7 +721,7 @@ __global__ __launch_bounds__(64 * kDqWaves, 1) void bwd_dq_kernel(DqArgs a) {
     qf[ks] = *(const bf16x8*)(a.q + base + (size_t)qr * tok + 16 * ks + 8 * hi);
     dof[ks] = *(const bf16x8*)(a.dout + base + (size_t)qr * tok + 16 * ks + 8 * hi);
   }
-  const float lse2 = a.lse2[bh * (size_t)a.ntile * kBN + qr];
+  const float nlse2 = a.nls[bh * (size_t)a.ntile * kBN + qr] * a.scale_log2;
   const float dd = a.dd[bh * (size_t)a.ntile * kBN + qr];
 
   f32x16 dq_acc[D / 32];
@@ -770,7 +818,7 @@ __global__ __launch_bounds__(64 * kDqWaves, 1) void bwd_dq_kernel(DqArgs a) {
       // Register r holds key k0 + kb*32 + 8*(r/4) + 4*hi + r%4 of this lane's query.
       float ds[16];
 #pragma unroll
-      for (int r = 0; r < 16; ++r) ds[r] = fast_exp2(fmaf(s[r], a.scale_log2, -lse2));
+      for (int r = 0; r < 16; ++r) ds[r] = fast_exp2(fmaf(s[r], a.scale_log2, nlse2));
       if (need_mask && plain_tile) {  // joint tile of real keys: the key mask's bits alone
         const unsigned bits = (unsigned)(kbits >> (32 * kb)) >> (4 * hi);
 #pragma unroll
@@ -866,14 +914,14 @@ __global__ void zero_f32_kernel(float* x, size_t n4) {
 
 }  // namespace
 
-hipError_t launch_bwd_prepare(const __bf16* o, const float* lse, const __bf16* dout, float* dd, float* lse2, int B,
-                              int H, int N, int Npad, int head_dim, hipStream_t s) {
+hipError_t launch_bwd_prepare(const __bf16* o, const float* lse, const __bf16* dout, float* dd, float* nls, int B,
+                              int H, int N, int Npad, int head_dim, float scale, hipStream_t s) {
   const size_t threads = std::max((size_t)B * N * H * (head_dim / 8), (size_t)B * H * (Npad - N));
   dim3 grid((unsigned)((threads + 255) / 256));
   if (head_dim == 128)
-    hipLaunchKernelGGL(bwd_prepare_kernel<128>, grid, dim3(256), 0, s, o, lse, dout, dd, lse2, B, H, N, Npad);
+    hipLaunchKernelGGL(bwd_prepare_kernel<128>, grid, dim3(256), 0, s, o, lse, dout, dd, nls, B, H, N, Npad, 1.0f / scale);
   else
-    hipLaunchKernelGGL(bwd_prepare_kernel<64>, grid, dim3(256), 0, s, o, lse, dout, dd, lse2, B, H, N, Npad);
+    hipLaunchKernelGGL(bwd_prepare_kernel<64>, grid, dim3(256), 0, s, o, lse, dout, dd, nls, B, H, N, Npad, 1.0f / scale);
   return hipGetLastError();
 }
 

@@ -78,6 +78,15 @@ __device__ __forceinline__ void copy16_to_lds_opaque(const void* g, VC_LDS void*
                : "memory");
 }
 
+// The same from a wave-uniform base plus a 32-bit byte offset per lane, so that a copy whose
+// lanes keep their offsets from tile to tile needs scalar address arithmetic only.
+__device__ __forceinline__ void copy16_to_lds_opaque(const void* base, unsigned lane_off, VC_LDS void* lds_wave_base) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+               :
+               : "s"(__builtin_amdgcn_readfirstlane((unsigned)(size_t)lds_wave_base)), "v"(lane_off), "s"(base)
+               : "memory");
+}
+
 // Waits for every outstanding memory operation of this wave (vector memory and LDS).
 __device__ __forceinline__ void wait_all_memory() { __builtin_amdgcn_s_waitcnt(0); }
 
@@ -108,6 +117,42 @@ struct RowTile {
 // half-wave) hits 64 distinct banks, while 16 consecutive tokens still occupy 16 distinct
 // rows of the run for the plain 16-byte reads.
 __host__ __device__ constexpr int perm_row(int t) { return (t & ~15) | ((t & 3) << 2) | ((t >> 2) & 3); }
+
+// Row-major bf16 rows in LDS without per-row padding, laid out so that every 1 KiB wave copy
+// is RPC whole rows: LDS row R sits in copy R / RPC, copies 1 KiB + PAD apart, and its
+// 16-byte chunk c in slot c ^ (R % RPC). The padding and the swizzle together spread over
+// distinct banks the 16 rows one quarter-wave reads at a common chunk and, with rows in
+// perm_row order, the 4 rows x 64 bytes of a half-wave's transposing read. As a copy's rows
+// start a fixed number of tokens apart, its lanes' offsets from the copy's first row are
+// the same for every copy and tile: the padded RowTile, whose copies cover 3.8 rows each,
+// needs a division and a 64-bit address per lane and copy (about 20 vector instructions).
+template <int D>
+struct SwzRows {
+  static constexpr int CPR = D / 8;                    // 16-byte chunks per row
+  static constexpr int RPC = 64 / CPR;                 // rows per wave copy
+  static constexpr int GS = 1024 + (D == 128 ? 64 : 128);  // byte stride of copies
+  static constexpr int bytes(int rows) { return rows / RPC * GS; }
+  static __device__ __forceinline__ int off(int R, int c) { return (R / RPC) * GS + (R % RPC) * 2 * D + ((c ^ (R % RPC)) << 4); }
+  // off(R, 2*ks + hi) = (off(R, hi) ^ 32 * (ks % NBASE)) + 64 * (ks / NBASE): bits 5 (and, at
+  // head_dim 64, 6) of off(R, hi) come from the chunk alone.
+  static constexpr int NBASE = RPC / 2;
+};
+
+// Wave copy `idx` of a swizzled row tile whose first row is token row0, its rows in LDS in
+// perm_row order (PERM) or token order, rows past N - 1 repeating it: the copy's first token
+// (uniform) and the lane's byte offset from it. LDS row RPC*idx + i holds token
+// perm_row(RPC*idx + i) = perm_row(RPC*idx) + perm_row(i).
+template <int D, bool PERM>
+__device__ __forceinline__ int swz_copy_row(int row0, int N, int idx) {
+  const int r = SwzRows<D>::RPC * idx;
+  return min(row0 + (PERM ? perm_row(r) : r), N - 1);
+}
+template <int D, bool PERM>
+__device__ __forceinline__ unsigned swz_copy_off(int first, unsigned tok, int N, unsigned lane) {
+  using S = SwzRows<D>;
+  const int i = lane / S::CPR, c = (lane % S::CPR) ^ i;  // row of the copy, source chunk
+  return __umul24(min(PERM ? perm_row(i) : i, N - 1 - first), tok) * 2 + c * 16;
+}
 
 // Issues wave copy `idx` of a row tile: rows row0 .. row0+63 of the [B, N, H, D] tensor
 // slice at src (row r at src + r*tok), rows clamped to N-1. The pad chunk of each row
@@ -273,16 +318,16 @@ struct AttendRule {
     const int lo = frame_start(v0), hi = min(N, frame_start(q1 - 1) + L);
     return TileRuns{text_tiles, lo / kTileTok, (hi + kTileTok - 1) / kTileTok, ntile};
   }
-  // Query tiles a workgroup of keys [k0, k1) visits (key-stationary kernels). Spatial: all
+  // Query tiles (of `per` rows, ntile in all) a workgroup of keys [k0, k1) visits. Spatial: all
   // video query tiles if it holds real text keys, else the tiles of its keys' frames; never
   // a tile of text queries only.
-  __device__ __forceinline__ TileRuns query_tiles(int k0, int k1, int ntile) const {
+  __device__ __forceinline__ TileRuns query_tiles(int k0, int k1, int ntile, int per) const {
     if (L == 0) return TileRuns{0, 0, ntile, ntile};
-    if (k0 < T && (km || k0 < tl)) return TileRuns{0, T / kTileTok, ntile, ntile};
+    if (k0 < T && (km || k0 < tl)) return TileRuns{0, T / per, ntile, ntile};
     const int v0 = max(k0, T);
     if (v0 >= k1) return TileRuns{0, 0, 0, ntile};
     const int lo = frame_start(v0), hi = min(N, frame_start(k1 - 1) + L);
-    return TileRuns{0, lo / kTileTok, (hi + kTileTok - 1) / kTileTok, ntile};
+    return TileRuns{0, lo / per, (hi + per - 1) / per, ntile};
   }
 };
 
@@ -298,15 +343,6 @@ __device__ __forceinline__ QueryRange query_range(const AttendRule& r, int i) {
   const int f0 = r.frame_start(i);
   return QueryRange{f0, f0 + r.L, true};
 }
-// Spatial branch, key side: the queries attending to key j, [lo, hi): every video query
-// for a text key, the queries of its frame for a video key.
-__device__ __forceinline__ int2 key_range(const AttendRule& r, int j) {
-  if (r.L == 0) return int2{0, 0};
-  if (j < r.T) return int2{r.T, r.N};
-  const int f0 = r.frame_start(min(j, r.N - 1));
-  return int2{f0, f0 + r.L};
-}
-
 // Kernel arguments. Token stride is H*D elements ([B, N, H, D] layout).
 struct FwdArgs {
   const __bf16* q;
@@ -332,9 +368,7 @@ struct DkdvArgs {
   const __bf16* k;
   const __bf16* v;
   const __bf16* dout;
-  const __bf16* qt;     // Q as transposed token tiles
-  const __bf16* dot;    // dO as transposed token tiles
-  const float* lse2;    // LSE * log2(e), +inf for rows without keys and padding, [B, H, Npad]
+  const float* nls;     // -LSE / scale, -inf for rows without keys and padding, [B, H, Npad]
   const float* dd;      // -D = -rowsum(dO o O), 0 on padding, [B, H, Npad]
   const int32_t* text_len;
   const uint8_t* key_mask;
@@ -358,8 +392,7 @@ struct DkdvArgs {
   // Joint attention with dQ fused in (dq_acc non-NULL): the workgroups of key blocks
   // [0, dq_blocks) also add their keys' share of dQ / scale, dS K, into the fp32
   // accumulator dq_acc ([B, N, H, D], zeroed by the launch) with atomics; the dQ pass adds
-  // the share of the other keys. qt and dot are not read (transposed operands come from the
-  // row-major tiles).
+  // the share of the other keys.
   float* dq_acc;
   int dq_blocks;
 };
@@ -373,7 +406,7 @@ struct DqArgs {
   const __bf16* v;
   const __bf16* dout;
   const __bf16* kt;     // K as transposed token tiles
-  const float* lse2;
+  const float* nls;
   const float* dd;
   const int32_t* text_len;
   const uint8_t* key_mask;
@@ -427,8 +460,8 @@ namespace vcja {
 // Writes the transposed token tiles of x ([B, N, H, D]) into xt.
 hipError_t launch_token_tiles(const __bf16* x, __bf16* xt, int B, int H, int N, int head_dim, hipStream_t s);
 hipError_t launch_fwd(const FwdArgs& a, int head_dim, hipStream_t s);
-hipError_t launch_bwd_prepare(const __bf16* o, const float* lse, const __bf16* dout, float* dd, float* lse2, int B,
-                              int H, int N, int Npad, int head_dim, hipStream_t s);
+hipError_t launch_bwd_prepare(const __bf16* o, const float* lse, const __bf16* dout, float* dd, float* nls, int B,
+                              int H, int N, int Npad, int head_dim, float scale, hipStream_t s);
 hipError_t launch_bwd_dkdv(const DkdvArgs& a, int head_dim, hipStream_t s);
 hipError_t launch_bwd_dq(const DqArgs& a, int head_dim, hipStream_t s);
 // dq = bf16(scale * acc) over n elements (a fused backward whose key blocks all added their

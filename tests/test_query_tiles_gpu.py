@@ -1,0 +1,32 @@
+"""GPU parity of the key-stationary backward at the edges of its query walk, against the fp64
+oracle: tiles of 32 queries (one row short, exact, one row over), the row statistics copied
+for 256 queries at a time, key blocks of 256, and dQ turns that do not divide the tile
+count. A wrong edge shifts or drops whole rows, far outside the bf16 bounds of
+parity_util (mean-rel 5e-3, max-abs 2e-2 or one bf16 spacing)."""
+import numpy as np
+import pytest
+
+import oracle.ref_attention as ora
+import workloads as W
+from parity_util import assert_close, bf16_values, run_gpu, to_gpu_bf16
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("det", [False, True], ids=["fused", "deterministic"])
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("tokens", [31, 32, 33, 64, 95, 255, 256, 257, 289, 513])
+def test_tile_edges(tokens, head_dim, det):
+    import paper_2501_08453_amd as vc
+    w = W.custom(2, 2, head_dim, 0, 1, 1, tokens)
+    x = W.make_inputs(w, seed=tokens + head_dim)
+    g = {n: to_gpu_bf16(x[n]) for n in ("q", "k", "v", "do")}
+    out = run_gpu(vc.desc_for(w, deterministic=det), g["q"], g["k"], g["v"], g["do"])
+    q, k, v, do = (bf16_values(g[n]) for n in ("q", "k", "v", "do"))
+    valid = np.ones((2, tokens), dtype=bool)
+    c = ora.default_scale(head_dim)
+    o, lse = ora.attention_forward(q, k, v, valid, c)
+    dq, dk, dv = ora.attention_backward(q, k, v, do, valid, c, lse=lse)
+    for name, a, r in (("O", out["o"], o), ("LSE", out["lse"], lse), ("dQ", out["dq"], dq), ("dK", out["dk"], dk),
+                       ("dV", out["dv"], dv)):
+        assert_close(name, a, r)
