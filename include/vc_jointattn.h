@@ -108,9 +108,13 @@ int64_t vc_jointattn_tokens(const vc_jointattn_desc* desc);
 
 /* Bytes of device workspace the forward needs: a token-major copy of V
  * ([B,H,ceil(N/64)] tiles of D x 72 bf16), then room for the fp32 partial
- * results of up to 256 workgroups of 256 query rows (O, exponent base, sum),
- * used when the work's last round of workgroups on the device is split over
- * several workgroups to end early. 0 for an invalid descriptor. Host only. */
+ * results of workgroups of 256 query rows (O, exponent base, sum), used when
+ * the work's last round of workgroups on the device is split over several
+ * workgroups to end early: one per 256-row block, head and sample, at most 256,
+ * or, where the best split of that round takes more, up to 512. A smaller
+ * workspace is accepted down to the former number (fewer workgroups then share
+ * the round; sums merged from another split round differently).
+ * 0 for an invalid descriptor. Host only. */
 size_t vc_jointattn_fwd_workspace_bytes(const vc_jointattn_desc* desc);
 
 /* Forward: o = softmax(c q k^T, masked) v and lse, as defined above.
@@ -148,11 +152,11 @@ vc_status vc_jointattn_fwd_noalloc(const vc_jointattn_desc* desc,
                                    void* o, float* lse, void* stream);
 
 /* Bytes of device workspace the backward needs: per query row fp32 -D and
- * LSE*log2(e) ([B,H,Npad], Npad = N rounded up to 64), token-major copies of
- * Q, dO and K (as for the forward's V; with desc->deterministic = 0 the same
- * region holds the fp32 dQ accumulator [B,N,H,D] instead), and room for fp32
- * partial dK, dV (or dQ) of up to 256 workgroups of 256 rows, used as in the
- * forward. 0 for an invalid descriptor. Host only. */
+ * -LSE/c ([B,H,Npad], Npad = N rounded up to 64), the size of three token-major
+ * copies (as of the forward's V: one of K, the others' place holds the fp32 dQ
+ * accumulator of desc->deterministic = 0), and room for fp32 partial dK, dV (or
+ * dQ) of workgroups of 256 rows, as many as and used as in the forward; smaller
+ * ones accepted as there. 0 for an invalid descriptor. Host only. */
 size_t vc_jointattn_bwd_workspace_bytes(const vc_jointattn_desc* desc);
 
 /* Backward: dq, dk, dv (bf16 [B,N,H,D]) from q, k, v, the forward's o and lse,

@@ -5,6 +5,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <initializer_list>
 #include <limits>
 #include <mutex>
 
@@ -110,31 +111,63 @@ size_t rows_bytes(const vc_jointattn_desc* d, int64_t n) {
 
 // Joint attention: split of the last, partial round of a kernel's dispatch. With W items
 // (256-row blocks x heads x samples) on `cus` compute units, the R = W mod cus items of the
-// last round are each split into C = cus / R workgroups over runs of `span` tiles along the
-// other token axis, so that the round ends after about 1/C of an item's time. At most
-// kTailMaxWgs split workgroups (the workspace is planned for that many).
-constexpr int kTailMaxWgs = 256;
+// last round (all of them when W < cus) can each be split into C workgroups over runs of
+// `span` tiles along the other token axis, whose fp32 partials are merged afterwards. With
+// `over` the tiles' worth of time a split workgroup spends on its partials and `merge` that
+// of the merge launch, the round takes ceil(R C / cus) (span + over) + merge tiles instead
+// of ntile: the C of least time is taken, if it saves at least a tenth. Measured (tile =
+// 64 tokens; forward, dQ: about 2 us a tile, dK/dV 3.4 us, 8 to 13 us to write a
+// workgroup's partials, 6 to 15 us a merge): see kSplit*. `max_wgs` bounds R C (workspace).
+struct SplitCost {
+  int over, merge;
+};
+constexpr SplitCost kSplitFwd{3, 5}, kSplitDkdv{5, 6}, kSplitDq{3, 5};
+constexpr int kTailMinWgs = 256;  // split workgroups the least accepted workspace has room for
+constexpr int kTailMaxWgs = 512;  // ... and the largest queried one
+constexpr int kPlanCus = 256;     // compute units the queries (which touch no device) assume
 constexpr int kRowsPerItem = 256;
 struct TailPlan {
   int items, chunks, span;
 };
-TailPlan tail_plan(int64_t work_items, int ntile, int cus) {
-  cus = std::min(cus, kTailMaxWgs);
-  if (cus < 2 || work_items <= cus) return TailPlan{0, 1, 0};
+TailPlan tail_plan(int64_t work_items, int ntile, int cus, SplitCost cost, int64_t max_wgs) {
+  const TailPlan none{0, 1, 0};
+  if (cus < 2) return none;
   const int r = (int)(work_items % cus);
-  if (r == 0 || cus / r < 2) return TailPlan{0, 1, 0};
-  const int span = (ntile + cus / r - 1) / (cus / r);
-  return TailPlan{r, (ntile + span - 1) / span, span};
+  if (r == 0) return none;
+  TailPlan best = none;
+  int64_t least = (int64_t)ntile * 9 / 10;
+  for (int c = 2; c <= std::min(ntile, 64) && (int64_t)r * c <= max_wgs; ++c) {
+    const int span = (ntile + c - 1) / c, chunks = (ntile + span - 1) / span;
+    const int64_t rounds = ((int64_t)r * chunks + cus - 1) / cus;
+    const int64_t t = rounds * (span + cost.over) + cost.merge;
+    if (t < least) {
+      least = t;
+      best = TailPlan{r, chunks, span};
+    }
+  }
+  return best;
 }
 // Items of the joint kernels (256-row blocks x heads x samples).
 int64_t joint_items(const vc_jointattn_desc* d, int64_t n) {
   return ((n + kRowsPerItem - 1) / kRowsPerItem) * d->heads * d->batch;
 }
-// fp32 partials of the split tail: dK and dV of up to kTailMaxWgs workgroups of 256 keys
-// (the dQ pass reuses the region for its single tensor).
+// Split workgroups that the queried workspaces have room for: the least accepted number, or
+// what the largest plan of these kernels takes.
+int64_t queried_wgs(const vc_jointattn_desc* d, int64_t n, std::initializer_list<SplitCost> costs) {
+  int64_t wgs = std::min<int64_t>(kTailMinWgs, joint_items(d, n));
+  for (const SplitCost& c : costs) {
+    const TailPlan t = tail_plan(joint_items(d, n), ntiles(n), kPlanCus, c, kTailMaxWgs);
+    wgs = std::max<int64_t>(wgs, (int64_t)t.items * t.chunks);
+  }
+  return wgs;
+}
+// fp32 partials of the split tail: dK and dV of `wgs` workgroups of 256 keys (the dQ pass
+// reuses the region for its single tensor). The least accepted region: kTailMinWgs of them,
+// or one per item where there are fewer; the plans take what the caller's workspace holds.
+constexpr size_t tail_wg_bytes(int head_dim) { return (size_t)2 * kRowsPerItem * head_dim * sizeof(float); }
 size_t tail_part_bytes(const vc_jointattn_desc* d, int64_t n) {
-  const int64_t wgs = std::min<int64_t>(kTailMaxWgs, joint_items(d, n));
-  return align256((size_t)2 * wgs * kRowsPerItem * d->head_dim * sizeof(float));
+  const int64_t wgs = std::min<int64_t>(kTailMinWgs, joint_items(d, n));
+  return align256(wgs * tail_wg_bytes(d->head_dim));
 }
 
 // Fused backward: the key blocks [0, fused_dq_blocks) add their dQ share with atomics in
@@ -165,11 +198,24 @@ bool all_keys_fused(const vc_jointattn_desc* d, int64_t n) {
 }
 
 // Forward workspace: V^T tiles | split-tail partials (unnormalised O, base, sum per row).
+constexpr size_t fwd_wg_bytes(int head_dim) { return (size_t)kRowsPerItem * (head_dim + 2) * sizeof(float); }
 size_t fwd_tail_bytes(const vc_jointattn_desc* d, int64_t n) {
-  const int64_t wgs = std::min<int64_t>(kTailMaxWgs, joint_items(d, n));
-  return align256((size_t)wgs * kRowsPerItem * (d->head_dim + 2) * sizeof(float));
+  const int64_t wgs = std::min<int64_t>(kTailMinWgs, joint_items(d, n));
+  return align256(wgs * fwd_wg_bytes(d->head_dim));
 }
 size_t fwd_ws_bytes(const vc_jointattn_desc* d, int64_t n) { return tiles_bytes(d, n) + fwd_tail_bytes(d, n); }
+// Split workgroups that a workspace of `have` bytes holds after its first `used` bytes.
+int64_t tail_wgs(size_t have, size_t used, size_t wg_bytes) {
+  return have <= used ? 0 : std::min<int64_t>(kTailMaxWgs, (int64_t)((have - used) / wg_bytes));
+}
+
+// The same for the forward, whose plan must not depend on which entry point provides the
+// workspace where the no-allocation one accepts the problem (their outputs are bitwise equal).
+int64_t fwd_tail_wgs(const vc_jointattn_desc* d, int64_t n, size_t have) {
+  if (fwd_ws_bytes(d, n) <= VC_JOINTATTN_NOALLOC_SCRATCH_BYTES)
+    have = std::min<size_t>(have, VC_JOINTATTN_NOALLOC_SCRATCH_BYTES);
+  return tail_wgs(have, tiles_bytes(d, n), fwd_wg_bytes(d->head_dim));
+}
 
 // Backward workspace: -D | -LSE/c | fp32 dQ accumulator (the size of two sets of token
 // tiles, >= 4 bytes per element of dq) | K^T tiles | tail partials.
@@ -182,6 +228,13 @@ struct BwdWorkspace {
 
 size_t bwd_ws_bytes(const vc_jointattn_desc* d, int64_t n) {
   return 2 * rows_bytes(d, n) + 3 * tiles_bytes(d, n) + tail_part_bytes(d, n);
+}
+size_t bwd_ws_query_bytes(const vc_jointattn_desc* d, int64_t n) {
+  return bwd_ws_bytes(d, n) - tail_part_bytes(d, n) +
+         align256(queried_wgs(d, n, {kSplitDkdv, kSplitDq}) * tail_wg_bytes(d->head_dim));
+}
+int64_t bwd_tail_wgs(const vc_jointattn_desc* d, int64_t n, size_t have) {
+  return tail_wgs(have, bwd_ws_bytes(d, n) - tail_part_bytes(d, n), tail_wg_bytes(d->head_dim));
 }
 float* tail_part_of(const vc_jointattn_desc* d, int64_t n, void* ws) {
   return reinterpret_cast<float*>(static_cast<char*>(ws) + 2 * rows_bytes(d, n) + 3 * tiles_bytes(d, n));
@@ -281,13 +334,13 @@ int64_t vc_jointattn_tokens(const vc_jointattn_desc* desc) {
 size_t vc_jointattn_fwd_workspace_bytes(const vc_jointattn_desc* desc) {
   int64_t n = 0;
   if (check_desc(desc, &n) != VC_OK) return 0;
-  return fwd_ws_bytes(desc, n);
+  return tiles_bytes(desc, n) + align256(queried_wgs(desc, n, {kSplitFwd}) * fwd_wg_bytes(desc->head_dim));
 }
 
 size_t vc_jointattn_bwd_workspace_bytes(const vc_jointattn_desc* desc) {
   int64_t n = 0;
   if (check_desc(desc, &n) != VC_OK) return 0;
-  return bwd_ws_bytes(desc, n);
+  return bwd_ws_query_bytes(desc, n);
 }
 
 int64_t vc_jointattn_fused_dq_keys(const vc_jointattn_desc* desc) {
@@ -300,7 +353,7 @@ int64_t vc_jointattn_fused_dq_keys(const vc_jointattn_desc* desc) {
 size_t vc_spatialattn_bwd_workspace_bytes(const vc_jointattn_desc* desc) {
   int64_t n = 0;
   if (check_desc(desc, &n) != VC_OK) return 0;
-  return spatial_bwd_ws_bytes(desc, n);
+  return std::max(spatial_bwd_ws_bytes(desc, n), bwd_ws_query_bytes(desc, n));
 }
 
 }  // extern "C"
@@ -341,7 +394,9 @@ vc_status fwd_impl(const vc_jointattn_desc* desc, const void* q, const void* k, 
   a.ntile = ntiles(n);
   a.frame_len = spatial ? desc->grid_h * desc->grid_w : 0;
   a.scale_log2 = scale_of(desc) * vcja::kLog2e;
-  const TailPlan tp = spatial ? TailPlan{0, 1, 0} : tail_plan(joint_items(desc, n), ntiles(n), device_cus());
+  const TailPlan tp = spatial ? TailPlan{0, 1, 0}
+                              : tail_plan(joint_items(desc, n), ntiles(n), device_cus(), kSplitFwd,
+                                          fwd_tail_wgs(desc, n, workspace_bytes));
   a.tail_part = reinterpret_cast<float*>(static_cast<char*>(workspace) + tiles_bytes(desc, n));
   a.tail_blocks = tp.items;
   a.tail_chunks = tp.chunks;
@@ -445,7 +500,9 @@ vc_status dkdv_impl(const vc_jointattn_desc* desc, const void* q, const void* k,
   a.text_blocks = ts.blocks;
   a.text_chunks = ts.chunks;
   a.text_span = ts.span;
-  const TailPlan tp = spatial ? TailPlan{0, 1, 0} : tail_plan(joint_items(desc, n), ntiles(n), device_cus());
+  const TailPlan tp = spatial ? TailPlan{0, 1, 0}
+                              : tail_plan(joint_items(desc, n), ntiles(n), device_cus(), kSplitDkdv,
+                                          bwd_tail_wgs(desc, n, workspace_bytes));
   a.tail_part = tail_part_of(desc, n, workspace);
   a.tail_blocks = tp.items;
   a.tail_chunks = tp.chunks;
@@ -515,7 +572,9 @@ vc_status dq_impl(const vc_jointattn_desc* desc, const void* q, const void* k, c
   a.text_len = text_len;
   a.key_mask = key_mask;
   a.dq = static_cast<__bf16*>(dq);
-  const TailPlan tp = spatial ? TailPlan{0, 1, 0} : tail_plan(joint_items(desc, n), ntiles(n), device_cus());
+  const TailPlan tp = spatial ? TailPlan{0, 1, 0}
+                              : tail_plan(joint_items(desc, n), ntiles(n) - a.kt_min, device_cus(), kSplitDq,
+                                          bwd_tail_wgs(desc, n, workspace_bytes));
   a.tail_part = tail_part_of(desc, n, workspace);
   a.tail_blocks = tp.items;
   a.tail_chunks = tp.chunks;

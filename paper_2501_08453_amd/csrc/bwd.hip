@@ -662,6 +662,7 @@ __global__ void tail_reduce_kernel(const float* part, __bf16* dk, __bf16* dv, in
   const int h = (item / nblk) % H, b = item / (nblk * H);
   const size_t stride = (size_t)items * chunks * kBKV * D;  // dK partials, then dV
   f32x4 sk = {0.0f, 0.0f, 0.0f, 0.0f}, sv = sk;
+#pragma unroll 4
   for (int c = 0; c < chunks; ++c) {
     const size_t off = (((size_t)slot * chunks + c) * kBKV + k) * D + d;
     sk += *(const f32x4*)(part + off);
@@ -742,7 +743,8 @@ __global__ __launch_bounds__(64 * kDqWaves, 1) void bwd_dq_kernel(DqArgs a) {
   const QueryRange qrange = query_range(rule, qi);
   // Key tiles this workgroup visits (the same sequence for every wave).
   TileRuns runs = rule.key_tiles(rb.r0, rb.r1, a.ntile);
-  const int kt0 = tail ? ti.chunk * a.tail_span : 0;  // joint tail: this chunk's key tiles
+  // Completing a fused backward: keys >= kt_min only; joint tail: this chunk's key tiles of them.
+  const int kt0 = a.kt_min + (tail ? ti.chunk * a.tail_span : 0);
   if (tail) {
     runs.a1 = min(runs.a1, kt0 + a.tail_span);
     runs.b1 = min(runs.b1, kt0 + a.tail_span);
@@ -773,7 +775,7 @@ __global__ __launch_bounds__(64 * kDqWaves, 1) void bwd_dq_kernel(DqArgs a) {
       copy16_to_lds_opaque(a.kt + (bh * a.ntile + kt) * tile_elems(D) + idx * 512 + lane * 8, sk + 2 * RT + idx * 1024);
   };
 
-  int kt = next_tile(max(kt0, a.kt_min));  // completing a fused backward: keys >= kt_min only
+  int kt = next_tile(kt0);
   if (kt < a.ntile) issue(kt, 0);
   // Key-mask bytes of each tile loaded a step ahead (waited for at the barrier with the
   // tile's copies), turned into the tile's bits there.
@@ -890,6 +892,7 @@ __global__ void tail_reduce_dq_kernel(const float* part, __bf16* dq, int B, int 
   if (row >= N) return;
   const int h = (item / nblk) % H, b = item / (nblk * H);
   f32x4 s = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 4
   for (int c = 0; c < chunks; ++c) s += *(const f32x4*)(part + (((size_t)slot * chunks + c) * kDqBM + k) * D + d);
   const size_t off = (((size_t)b * N + row) * H + h) * D + d;
   if (dq_acc) s += scale * *(const f32x4*)(dq_acc + off);  // the fused keys' share (unscaled)

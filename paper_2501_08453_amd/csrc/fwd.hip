@@ -451,20 +451,24 @@ __global__ void tail_merge_kernel(const float* part, __bf16* o, float* lse, int 
   const size_t rows = (size_t)items * chunks * kBM;
   const float* pm = part + rows * D;
   const float* pl = pm + rows;
+  const float* pm0 = pm + (size_t)slot * chunks * kBM + k;
+  const float* pl0 = pl + (size_t)slot * chunks * kBM + k;
+  const float* po0 = part + ((size_t)slot * chunks * kBM + k) * D + d;
   float mx = -INFINITY;
-  for (int c = 0; c < chunks; ++c) {
-    const size_t r = ((size_t)slot * chunks + c) * kBM + k;
-    if (pl[r] > 0.0f) mx = fmaxf(mx, pm[r]);
-  }
+  // Branch-free, so that the loads of several chunks are in flight together.
+#pragma unroll 4
+  for (int c = 0; c < chunks; ++c) mx = fmaxf(mx, pl0[(size_t)c * kBM] > 0.0f ? pm0[(size_t)c * kBM] : -INFINITY);
   float sum = 0.0f;
   f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 4
   for (int c = 0; c < chunks; ++c) {
-    const size_t r = ((size_t)slot * chunks + c) * kBM + k;
-    if (pl[r] > 0.0f) {
-      const float wgt = exp2f(pm[r] - mx);
-      sum += wgt * pl[r];
-      acc += wgt * *(const f32x4*)(part + r * D + d);
-    }
+    const float l = pl0[(size_t)c * kBM];
+    const float wgt = exp2f(pm0[(size_t)c * kBM] - mx);
+    const f32x4 x = *(const f32x4*)(po0 + (size_t)c * kBM * D);
+    const bool any = l > 0.0f;
+    sum += any ? wgt * l : 0.0f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc[e] += any ? wgt * x[e] : 0.0f;
   }
   const float inv = sum > 0.0f ? 1.0f / sum : 0.0f;
   const size_t off = (((size_t)b * N + row) * H + h) * D + d;

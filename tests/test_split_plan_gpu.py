@@ -1,0 +1,61 @@
+"""GPU parity of joint attention whose items (256-row blocks x heads x samples) are fewer than
+the compute units, or leave more than half of them in the last round, so that items are split
+into runs of tiles with fp32 partials (merged or summed afterwards), against the fp64 oracle:
+ragged last chunks, padded captions and masked keys inside chunks. The workspace the queries
+name and the least one that calls accept (room for fewer split workgroups) both give results
+inside the bf16 bounds of parity_util."""
+import numpy as np
+import pytest
+
+import oracle.ref_attention as ora
+import workloads as W
+from parity_util import assert_close, bf16_values, to_gpu_bf16
+
+pytestmark = pytest.mark.gpu
+
+# batch, heads, head_dim, text slot, frames, grid: on 256 compute units
+SHAPES = [
+    (1, 2, 128, 77, 4, 20, 31),    # 22 items of 40 tiles
+    (2, 1, 64, 100, 3, 30, 41),    # 30 items of 60 tiles
+    (1, 13, 64, 16, 6, 30, 31),    # 286 items: 30 in the last round
+]
+
+
+def _least_workspaces(B, H, D, N):
+    up = lambda x: (x + 255) & ~255  # noqa: E731
+    nt = (N + 63) // 64
+    tiles, rows = up(B * H * nt * D * 72 * 2), up(B * H * nt * 64 * 4)
+    wgs = min(256, (N + 255) // 256 * H * B)
+    return tiles + up(wgs * 256 * (D + 2) * 4), 2 * rows + 3 * tiles + up(2 * wgs * 256 * D * 4)
+
+
+@pytest.mark.parametrize("det", [False, True], ids=["fused", "deterministic"])
+@pytest.mark.parametrize("least", [False, True], ids=["queried", "least"])
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_split_items(shape, least, det):
+    import torch
+    import paper_2501_08453_amd as vc
+    w = W.custom(*shape, ragged_text=True)
+    B, N, H, D = w.shape
+    x = W.make_inputs(w, seed=N + D)
+    km = W.random_key_mask(w, 5, 0.8)
+    g = {n: to_gpu_bf16(x[n]) for n in ("q", "k", "v", "do")}
+    tl, kmt = torch.from_numpy(x["text_len"]).to("cuda"), torch.from_numpy(km).to("cuda")
+    desc = vc.desc_for(w, deterministic=det)
+    fws, bws = vc.vc_jointattn_fwd_workspace_bytes(desc), vc.vc_jointattn_bwd_workspace_bytes(desc)
+    lf, lb = _least_workspaces(B, H, D, N)
+    assert lf <= fws and lb <= bws
+    if least:
+        fws, bws = lf, lb
+    fws, bws = (torch.empty(n, dtype=torch.uint8, device="cuda") for n in (fws, bws))
+    o, lse = vc.fwd(g["q"], g["k"], g["v"], desc, tl, kmt, ws=fws)
+    dq, dk, dv = vc.bwd(g["q"], g["k"], g["v"], o, lse, g["do"], desc, tl, kmt, ws=bws)
+    torch.cuda.synchronize()
+    q, k, v, do = (bf16_values(g[n]) for n in ("q", "k", "v", "do"))
+    valid = ora.key_validity(B, N, w.text_slot, x["text_len"], km)
+    c = ora.default_scale(D)
+    ro, rl = ora.attention_forward(q, k, v, valid, c)
+    rdq, rdk, rdv = ora.attention_backward(q, k, v, do, valid, c, lse=rl)
+    assert_close("LSE", lse.cpu().numpy().astype(np.float64), rl)
+    for n, a, r in (("O", o, ro), ("dQ", dq, rdq), ("dK", dk, rdk), ("dV", dv, rdv)):
+        assert_close(n, bf16_values(a), r)
