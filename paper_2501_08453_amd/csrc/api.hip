@@ -353,7 +353,7 @@ int64_t vc_jointattn_fused_dq_keys(const vc_jointattn_desc* desc) {
 size_t vc_spatialattn_bwd_workspace_bytes(const vc_jointattn_desc* desc) {
   int64_t n = 0;
   if (check_desc(desc, &n) != VC_OK) return 0;
-  return std::max(spatial_bwd_ws_bytes(desc, n), bwd_ws_query_bytes(desc, n));
+  return bwd_ws_query_bytes(desc, n) + text_part_bytes(desc, n);
 }
 
 }  // extern "C"
