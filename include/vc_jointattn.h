@@ -106,8 +106,9 @@ const char* vc_status_string(int status);
  * vc_status if the descriptor is invalid. Host only; touches no device. */
 int64_t vc_jointattn_tokens(const vc_jointattn_desc* desc);
 
-/* Bytes of device workspace the forward needs: a token-major copy of V
- * ([B,H,ceil(N/64)] tiles of D x 72 bf16), then room for the fp32 partial
+/* Bytes of device workspace the forward needs: the size of a token-major copy of V
+ * ([B,H,ceil(N/64)] tiles of D x 72 bf16; kept from earlier versions, no longer
+ * written), then room for the fp32 partial
  * results of workgroups of 256 query rows (O, exponent base, sum), used when
  * the work's last round of workgroups on the device is split over several
  * workgroups to end early: one per 256-row block, head and sample, at most 256,

@@ -375,14 +375,10 @@ vc_status fwd_impl(const vc_jointattn_desc* desc, const void* q, const void* k, 
     return VC_ERR_ALIGN;
   if ((st = check_ws(workspace, workspace_bytes, fwd_ws_bytes(desc, n))) != VC_OK) return st;
   if ((st = check_device()) != VC_OK) return st;
-  __bf16* vt = static_cast<__bf16*>(workspace);
-  if (vcja::launch_token_tiles(bf(v), vt, desc->batch, desc->heads, (int)n, desc->head_dim, as_stream(stream)) !=
-      hipSuccess)
-    return VC_ERR_HIP;
   vcja::FwdArgs a;
   a.q = bf(q);
   a.k = bf(k);
-  a.vt = vt;
+  a.v = bf(v);
   a.text_len = text_len;
   a.key_mask = key_mask;
   a.o = static_cast<__bf16*>(o);

@@ -334,23 +334,10 @@ __global__ __launch_bounds__(64 * kDkdvWaves, 1) void bwd_dkdv_kernel(DkdvArgs a
   constexpr int DQ_STEPS = kBKV / 16;
   constexpr int DQ_TURNS = kDkdvWaves / NB;
   const int dq_turn = w / NB, dq_db = w % NB;
-  // Operand reads from a tile's swizzled rows, as one per-lane base each that a fixed XOR
-  // (formed where it is used, so that no further register is held) turns into the others:
-  // Plain reads of the A operands Q, dO: the lane's query row, chunk 2*ks + hi.
-  const int row_base = Rows::off(perm_row(l32), hi);
-  auto row_at = [](const VC_LDS char* p, int ks) {  // p = tile + row_base
-    return (const VC_LDS char*)((unsigned)(size_t)p ^ (32u * (ks % Rows::NBASE))) + ks / Rows::NBASE * 64;
-  };
-  // Transposing reads of the A operands Q^T, dO^T (rows in perm_row order): lane l of 16-lane
-  // group G supplies query 16*st2 + 8*part + 4*hi + (l%16)/4 and dims 32*db + 16*(G%2) +
-  // 4*(l%4) .. +3. Part 1 lies two LDS rows on, its chunks' swizzle differing by 2.
-  constexpr int TGS = 16 / Rows::RPC * Rows::GS;  // bytes between k-steps (16 rows)
-  const int tr_base =
-      Rows::off(perm_row(4 * hi + ((lane & 15) >> 2)), 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) + 8 * (lane & 1);
-  auto tr_at = [](const VC_LDS char* p, int st2, int db, int part) {  // p = tile + tr_base
-    const unsigned x = (D == 64 ? 64u * db : 0u) ^ (32u * part);
-    return (const VC_LDS char*)((unsigned)(size_t)p ^ x) + st2 * TGS + part * 4 * D + (D == 64 ? 0 : 64 * db);
-  };
+  // Bases of the operand reads: plain (the lane's query row) and transposing.
+  using Reads = SwzReads<D>;
+  const int row_base = Reads::row_base(perm_row(l32), hi);
+  const int tr_base = Reads::tr_base(lane);
 
   // dQ block of the tile starting at query row0, whose dS^T is in buffer `buf`: A = dS
   // (queries x keys) by transposing reads of dS^T, B = K from K^T. Lane l of 16-lane group G
@@ -437,16 +424,14 @@ __global__ __launch_bounds__(64 * kDkdvWaves, 1) void bwd_dkdv_kernel(DkdvArgs a
       f32x16 s, dp;
       bf16x8 f[2 * KSN];
       auto rd = [&](int i) {
-        f[i] = *(const VC_LDS bf16x8*)(row_at(q_lds + row_base, i % KSN) + (i < KSN ? 0 : RT));
+        f[i] = *(const VC_LDS bf16x8*)(Reads::row_at(q_lds + row_base, i % KSN) + (i < KSN ? 0 : RT));
       };
       // Operand element t of k-step st2 is query 16*st2 + 8*(t/4) + 4*hi + t%4, read from the
       // row-major tiles by two transposing reads (queries +0..3 and +8..11). Operand i: dO^T,
       // then Q^T, k-step st2 = (i / NB) % 2 major, dim block i % NB minor.
       bf16x8 g[4 * NB];
       auto rdt = [&](int i) {
-        const int o = i < 2 * NB ? RT : 0;
-        g[i] = cat4(lds_read_tr(tr_at(q_lds + tr_base, i / NB % 2, i % NB, 0) + o),
-                    lds_read_tr(tr_at(q_lds + tr_base, i / NB % 2, i % NB, 1) + o));
+        g[i] = Reads::tr_operand(q_lds + (i < 2 * NB ? RT : 0) + tr_base, i / NB % 2, i % NB);
       };
       // Register r holds query row 8*(r/4) + 4*hi + r%4 of the tile: four runs of 4 rows.
       auto form_p = [&](int r) {

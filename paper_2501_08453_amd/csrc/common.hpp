@@ -154,6 +154,50 @@ __device__ __forceinline__ unsigned swz_copy_off(int first, unsigned tok, int N,
   return __umul24(min(PERM ? perm_row(i) : i, N - 1 - first), tok) * 2 + c * 16;
 }
 
+// The lane's parts of such a copy's offsets, for kernels with registers to keep them: its row's
+// distance from the copy's first row and its source chunk, in bytes. offset() clamps the
+// row: a copy's rows past N - 1 repeat it.
+template <int D, bool PERM>
+struct SwzCopy {
+  unsigned row, chunk;
+  __device__ __forceinline__ SwzCopy(unsigned tok, int lane) {
+    using S = SwzRows<D>;
+    const int i = lane / S::CPR;
+    row = (unsigned)(PERM ? perm_row(i) : i) * tok * 2;
+    chunk = ((lane % S::CPR) ^ i) * 16;
+  }
+  __device__ __forceinline__ unsigned offset(int first, int N, unsigned tok) const {
+    return min(row, (unsigned)min(N - 1 - first, 15) * tok * 2) + chunk;
+  }
+};
+
+// Operand reads from a tile's swizzled rows: a per-lane base each, which a fixed XOR (formed
+// where it is used, so that no further register is held) turns into the others.
+template <int D>
+struct SwzReads {
+  using S = SwzRows<D>;
+  // Plain operand (m = row, k = dims 16*ks + 8*hi ..): chunk 2*ks + hi of the lane's row.
+  static __device__ __forceinline__ int row_base(int row, int hi) { return S::off(row, hi); }
+  static __device__ __forceinline__ const VC_LDS char* row_at(const VC_LDS char* p, int ks) {  // p = tile + row_base
+    return (const VC_LDS char*)((unsigned)(size_t)p ^ (32u * (ks % S::NBASE))) + ks / S::NBASE * 64;
+  }
+  // Transposed operand (m = dim, k = row) of rows in perm_row order by two transposing reads,
+  // parts 0 and 1: lane l of 16-lane group G supplies token 16*st + 8*part + 4*hi + (l%16)/4 and
+  // dims 32*db + 16*(G%2) + 4*(l%4) .. +3. Part 1 lies two LDS rows on, its chunks' swizzle
+  // differing by 2.
+  static constexpr int TGS = 16 / S::RPC * S::GS;  // bytes between k-steps (16 rows)
+  static __device__ __forceinline__ int tr_base(int lane) {
+    return S::off(perm_row(4 * (lane >> 5) + ((lane & 15) >> 2)), 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) + 8 * (lane & 1);
+  }
+  static __device__ __forceinline__ const VC_LDS char* tr_at(const VC_LDS char* p, int st, int db, int part) {
+    const unsigned x = (D == 64 ? 64u * db : 0u) ^ (32u * part);
+    return (const VC_LDS char*)((unsigned)(size_t)p ^ x) + st * TGS + part * 4 * D + (D == 64 ? 0 : 64 * db);
+  }
+  static __device__ __forceinline__ bf16x8 tr_operand(const VC_LDS char* p, int st, int db) {  // p = tile + tr_base
+    return cat4(lds_read_tr(tr_at(p, st, db, 0)), lds_read_tr(tr_at(p, st, db, 1)));
+  }
+};
+
 // Issues wave copy `idx` of a row tile: rows row0 .. row0+63 of the [B, N, H, D] tensor
 // slice at src (row r at src + r*tok), rows clamped to N-1. The pad chunk of each row
 // repeats the row's last chunk. PERM: the tile's rows in perm_row order.
@@ -347,7 +391,7 @@ __device__ __forceinline__ QueryRange query_range(const AttendRule& r, int i) {
 struct FwdArgs {
   const __bf16* q;
   const __bf16* k;
-  const __bf16* vt;     // V as transposed token tiles
+  const __bf16* v;
   const int32_t* text_len;
   const uint8_t* key_mask;
   __bf16* o;

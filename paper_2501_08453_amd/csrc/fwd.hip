@@ -1,13 +1,16 @@
 // Forward joint text-video attention for gfx950.
 //
 // One workgroup of eight waves owns 256 queries of one (sample, head); each
-// wave owns 32 of them, held in registers. Keys stream through LDS as
-// row-major tiles of 64 (rows padded by 16 bytes) and values as transposed
-// token tiles (prepared by a reformatting pass), both copied asynchronously
-// global -> LDS. Scores read the K tile one step before the P V products read
-// the V^T tile of the same keys, so each has its own two-slot ring (tile t in
-// slot t mod 2): the copies of step j+1 are in flight during step j, and one
-// barrier per tile suffices. All eight waves share each tile. Each wave issues its
+// wave owns 32 of them, held in registers. Keys and values stream through LDS as
+// row-major tiles of 64 (swizzled rows, see SwzRows: a copy needs scalar address
+// arithmetic only), copied asynchronously global -> LDS; the values' rows lie in
+// permuted order, so that the transposing LDS reads of V^T run at the rate of plain
+// ones and no transposed copy of V is made beforehand. (That copy's pass took 138 us of a
+// 2.95 ms spatial forward at 24 heads x 57,856 tokens and one launch of every small call;
+// the kernel itself is 2-5% faster on frames and at D = 64, unchanged on long sequences.) Scores read the K tile one step
+// before the P V products read the V tile of the same keys, so each has its own two-slot
+// ring (tile t in slot t mod 2): the copies of step j+1 are in flight during step j, and
+// one barrier per tile suffices. All eight waves share each tile. Each wave issues its
 // share of those copies between its score products rather than all at the top of
 // the step, where eight waves' worth of copy instructions would stall the start of
 // the matrix-core work.
@@ -44,10 +47,10 @@ constexpr float kSumLimit = 8192.0f;  // largest accepted sum of a lane's 32 pro
 
 template <int D>
 struct FwdTile {
-  static constexpr int KT = RowTile<D>::kBytes;       // K tile bytes
-  static constexpr int KS = RowTile<D>::kStride;      // K row stride
-  static constexpr int VTB = (int)tile_elems(D) * 2;  // V^T tile bytes
-  static constexpr int LDS = 2 * KT + 2 * VTB;        // K ring | V^T ring
+  using Rows = SwzRows<D>;
+  static constexpr int KT = Rows::bytes(kBN);         // K or V tile bytes
+  static constexpr int COPIES = kBN / Rows::RPC;      // wave copies of a tile
+  static constexpr int LDS = 4 * KT;                  // K ring | V ring
 };
 
 struct NoHook {
@@ -58,16 +61,15 @@ struct NoHook {
 // B = this wave's Q^T fragments, K fragments read two k-steps ahead of their products.
 // hook(j) runs after k-step 2j+1 (j < D/32).
 template <int D, class Hook = NoHook>
-__device__ __forceinline__ void scores(const VC_LDS char* ks_lds, const bf16x8* qf, int l32, int hi, f32x16* s,
-                                       Hook hook = Hook()) {
-  constexpr int KS = FwdTile<D>::KS;
+__device__ __forceinline__ void scores(const VC_LDS char* k_base, const bf16x8* qf, f32x16* s, Hook hook = Hook()) {
+  // k_base: the tile + the base of the lane's key row l32; key block 1 lies 32 rows on
 #pragma unroll
   for (int kb = 0; kb < 2; ++kb) s[kb] = zero_f32x16();
   constexpr int KSN = D / 16;
   bf16x8 f[KSN][2];
   auto rd = [&](int ks) {
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb) f[ks][kb] = *(const VC_LDS bf16x8*)(ks_lds + (kb * 32 + l32) * KS + (2 * ks + hi) * 16);
+    for (int kb = 0; kb < 2; ++kb) f[ks][kb] = *(const VC_LDS bf16x8*)(SwzReads<D>::row_at(k_base, ks) + kb * SwzRows<D>::bytes(32));
   };
   rd(0);
   rd(1);
@@ -82,22 +84,14 @@ __device__ __forceinline__ void scores(const VC_LDS char* ks_lds, const bf16x8* 
   sched_fence();
 }
 
-// O^T += V^T P^T for one 64-key tile. Operand element t of k-step st2 (lane half hi) is
-// key 16*st2 + 8*(t/4) + 4*hi + t%4, stored by the transposed tile as 8 consecutive
-// elements at position 16*st2 + 8*hi.
+// O^T += V^T P^T for one 64-key tile (v_base: the tile + the base of its transposing reads).
+// Operand element t of k-step c (lane half hi) is key 16*c + 8*(t/4) + 4*hi + t%4.
 template <int D>
-__device__ __forceinline__ void accumulate_pv(const VC_LDS char* vt_lds, const bf16x8* pb, int l32, int hi,
-                                              f32x16* oacc) {
+__device__ __forceinline__ void accumulate_pv(const VC_LDS char* v_base, const bf16x8* pb, f32x16* oacc) {
 #pragma unroll
-  for (int kb = 0; kb < 2; ++kb)
+  for (int c = 0; c < 4; ++c)
 #pragma unroll
-    for (int st2 = 0; st2 < 2; ++st2)
-#pragma unroll
-      for (int db = 0; db < D / 32; ++db) {
-        const bf16x8 af =
-            *(const VC_LDS bf16x8*)(vt_lds + ((db * 32 + l32) * kTileRow + kb * 32 + 16 * st2 + 8 * hi) * 2);
-        oacc[db] = mfma32(af, pb[2 * kb + st2], oacc[db]);
-      }
+    for (int db = 0; db < D / 32; ++db) oacc[db] = mfma32(SwzReads<D>::tr_operand(v_base, c, db), pb[c], oacc[db]);
 }
 
 // Masking of one wave's score tiles (lane = query qi).
@@ -186,12 +180,11 @@ __device__ __forceinline__ float raise_base(const f32x16* s, float scale_log2, b
   return alpha;
 }
 
-// V^T operand fragments of PV chunk c (key block c/2, k-step c%2) for every dim block.
+// V^T operand fragments of PV chunk c (keys 16*c .. +15) for every dim block.
 template <int D>
-__device__ __forceinline__ void load_vt_chunk(const VC_LDS char* vt_lds, int c, int l32, int hi, bf16x8* f) {
+__device__ __forceinline__ void load_vt_chunk(const VC_LDS char* v_base, int c, bf16x8* f) {
 #pragma unroll
-  for (int db = 0; db < D / 32; ++db)
-    f[db] = *(const VC_LDS bf16x8*)(vt_lds + ((db * 32 + l32) * kTileRow + (c >> 1) * 32 + 16 * (c & 1) + 8 * hi) * 2);
+  for (int db = 0; db < D / 32; ++db) f[db] = SwzReads<D>::tr_operand(v_base, c, db);
 }
 
 // KM: a key mask is given (a separate instance, so that the unmasked one carries none of
@@ -199,10 +192,8 @@ __device__ __forceinline__ void load_vt_chunk(const VC_LDS char* vt_lds, int c, 
 template <int D, bool KM>
 __global__ __launch_bounds__(64 * kWaves, kWavesPerSimd * 4 / kWaves) void fwd_kernel(FwdArgs a) {
   constexpr int KT = FwdTile<D>::KT;
-  constexpr int VTB = FwdTile<D>::VTB;
-  constexpr int KCOPIES = RowTile<D>::kCopies;  // 1 KiB wave copies per tile
-  constexpr int VCOPIES = VTB / 1024;
-  static_assert(VTB % 1024 == 0, "transposed tile must be whole wave copies");
+  using Rows = SwzRows<D>;
+  using Reads = SwzReads<D>;
   __shared__ __attribute__((aligned(1024))) char smem[FwdTile<D>::LDS];
 
   const int tid = threadIdx.x;
@@ -228,7 +219,6 @@ __global__ __launch_bounds__(64 * kWaves, kWavesPerSimd * 4 / kWaves) void fwd_k
   const int N = a.N;
   const size_t tok = (size_t)a.H * D;
   const size_t base = (size_t)b * N * tok + (size_t)h * D;
-  const __bf16* vt_bh = a.vt + ((size_t)b * a.H + h) * a.ntile * tile_elems(D);
   // This workgroup's queries (spatial branch: inside one frame; text rows are written
   // by the caller's text-rows pass).
   const RowBlock rb = row_block(gx, N, a.T, a.frame_len, kBM, false);
@@ -267,35 +257,29 @@ __global__ __launch_bounds__(64 * kWaves, kWavesPerSimd * 4 / kWaves) void fwd_k
     runs.b1 = min(runs.b1, kt0 + a.tail_span);
   }
   auto next_tile = [&](int kt) { return runs.next(kt); };
-  // Copies tile kt's K rows (rows past N repeat row N-1 and are masked) or V^T tile into
-  // ring slot `slot`. The copies are issued through inline assembly, so the compiler
-  // neither waits for them nor lets them force full waits on LDS reads; the kernel waits
-  // for them itself (wait_all_memory) before the barrier after which they are read.
-  auto issue_k = [&](int kt, int slot) {
-    VC_LDS char* dst = (VC_LDS char*)smem + slot * KT;
-    for (int idx = w; idx < KCOPIES; idx += kWaves) copy_row_tile<D, true>(a.k + base, tok, kt * kBN, N, dst, idx, lane);
-  };
-  auto issue_v = [&](int kt, int slot) {
-    VC_LDS char* dst = (VC_LDS char*)smem + 2 * KT + slot * VTB;
-    const __bf16* vsrc = vt_bh + (size_t)kt * tile_elems(D);
-    for (int idx = w; idx < VCOPIES; idx += kWaves) copy16_to_lds_opaque(vsrc + idx * 512 + lane * 8, dst + idx * 1024);
-  };
-  // The j-th K or V^T copy of this wave (a no-op past the tile), issued from the score
-  // loop's hook.
-  static_assert((KCOPIES + kWaves - 1) / kWaves <= D / 32 && (VCOPIES + kWaves - 1) / kWaves <= D / 32,
-                "every copy of a wave needs a hook slot");
+  // This wave's j-th copy of tile kt's K or V rows into ring slot `slot` (rows past N repeat
+  // row N-1: such keys are masked, such values zeroed before use). The copies are issued
+  // through inline assembly, so the compiler neither waits for them nor lets them force full
+  // waits on LDS reads; the kernel waits for them itself (wait_all_memory) before the barrier
+  // after which they are read.
+  constexpr int CPW = FwdTile<D>::COPIES / kWaves;  // copies per wave and tile
+  static_assert(CPW * kWaves == FwdTile<D>::COPIES && 2 * CPW == D / 32, "one copy per hook slot");
+  const unsigned tok32 = (unsigned)tok;
+  const SwzCopy<D, false> kc(tok32, lane);
+  const SwzCopy<D, true> vc(tok32, lane);
   auto k_copy = [&](int j, int kt, int slot) {
-    const int idx = w + j * kWaves;
-    if (idx < KCOPIES) copy_row_tile<D, true>(a.k + base, tok, kt * kBN, N, (VC_LDS char*)smem + slot * KT, idx, lane);
+    const int idx = w + j * kWaves, first = swz_copy_row<D, false>(kt * kBN, N, idx);
+    copy16_to_lds_opaque(a.k + base + (size_t)first * tok, kc.offset(first, N, tok32),
+                         (VC_LDS char*)smem + slot * KT + idx * Rows::GS);
   };
   auto v_copy = [&](int j, int kt, int slot) {
-    const int idx = w + j * kWaves;
-    if (idx < VCOPIES)
-      copy16_to_lds_opaque(vt_bh + (size_t)kt * tile_elems(D) + idx * 512 + lane * 8,
-                           (VC_LDS char*)smem + 2 * KT + slot * VTB + idx * 1024);
+    const int idx = w + j * kWaves, first = swz_copy_row<D, true>(kt * kBN, N, idx);
+    copy16_to_lds_opaque(a.v + base + (size_t)first * tok, vc.offset(first, N, tok32),
+                         (VC_LDS char*)smem + (2 + slot) * KT + idx * Rows::GS);
   };
-  auto k_slot = [&](int slot) { return (const VC_LDS char*)smem + slot * KT; };
-  auto v_slot = [&](int slot) { return (const VC_LDS char*)smem + 2 * KT + slot * VTB; };
+  const int krow = Reads::row_base(l32, hi), vtr = Reads::tr_base(lane);
+  auto k_slot = [&](int slot) { return (const VC_LDS char*)smem + slot * KT + krow; };
+  auto v_slot = [&](int slot) { return (const VC_LDS char*)smem + (2 + slot) * KT + vtr; };
 
   f32x16 oacc[D / 32];
 #pragma unroll
@@ -308,9 +292,12 @@ __global__ __launch_bounds__(64 * kWaves, kWavesPerSimd * 4 / kWaves) void fwd_k
   if (cur < a.ntile) {
     int nxt = next_tile(cur + 1);
     int par = 0;  // ring slot of tile `cur`
-    issue_k(cur, 0);
-    issue_v(cur, 0);
-    if (nxt < a.ntile) issue_k(nxt, 1);
+#pragma unroll
+    for (int j = 0; j < CPW; ++j) {
+      k_copy(j, cur, 0);
+      v_copy(j, cur, 0);
+      if (nxt < a.ntile) k_copy(j, nxt, 1);
+    }
     // Key-mask bytes of `cur` now and of each next tile a step ahead: their waits are the
     // ones before the barriers (a byte loaded and used in the same step would wait for the
     // step's tile copies too).
@@ -321,7 +308,7 @@ __global__ __launch_bounds__(64 * kWaves, kWavesPerSimd * 4 / kWaves) void fwd_k
     // Prologue: scores and softmax of the first tile.
     {
       f32x16 s[2];
-      scores<D>(k_slot(0), qf, l32, hi, s);
+      scores<D>(k_slot(0), qf, s);
       if (mask.tile_needs_mask(cur * kBN)) mask.apply<KM>(s, cur * kBN, hi, KM ? key_mask_bits(kmb_cur) : ~0ull);
       raise_base(s, a.scale_log2, true, m, pb, l);
     }
@@ -336,7 +323,7 @@ __global__ __launch_bounds__(64 * kWaves, kWavesPerSimd * 4 / kWaves) void fwd_k
     while (nxt < a.ntile) {
       const int nn = next_tile(nxt + 1);
       wait_all_memory();
-      __syncthreads();  // K of `nxt` and V^T of `cur` landed; K of `cur` and V^T of the
+      __syncthreads();  // K of `nxt` and V of `cur` landed; K of `cur` and V of the
                         // previous tile are no longer read by any wave
       const unsigned long long kbits = KM ? key_mask_bits(kmb_nxt) : ~0ull;  // key mask of `nxt`
       if (KM && nn < a.ntile) kmb_nxt = mask.rule.key_mask_byte(nn, lane);
@@ -346,10 +333,14 @@ __global__ __launch_bounds__(64 * kWaves, kWavesPerSimd * 4 / kWaves) void fwd_k
       }
       f32x16 s[2];
       // The copies of this step go to the slots freed by the barrier: K of `nn` to the
-      // slot of K of `cur`, V^T of `nxt` to the slot of the previous V^T tile.
-      scores<D>(k_slot(par ^ 1), qf, l32, hi, s, [&](int j) {
-        if (nn < a.ntile) k_copy(j, nn, par);
-        v_copy(j, nxt, par ^ 1);
+      // slot of K of `cur` (past the last tile: `nxt` again, never read), V of `nxt` to the
+      // slot of the previous V tile.
+      const int kn = nn < a.ntile ? nn : nxt;
+      scores<D>(k_slot(par ^ 1), qf, s, [&](int j) {
+        if (j % 2 == 0)
+          k_copy(j / 2, kn, par);
+        else
+          v_copy(j / 2, nxt, par ^ 1);
       });
       if (mask.tile_needs_mask(nxt * kBN)) mask.apply<KM>(s, nxt * kBN, hi, kbits);
       // P V of `cur` in four chunks of D/32 products; between them the vector ALUs do
@@ -357,18 +348,18 @@ __global__ __launch_bounds__(64 * kWaves, kWavesPerSimd * 4 / kWaves) void fwd_k
       // chunk. Fragments of the next chunk are read one chunk ahead.
       const VC_LDS char* vt_lds = v_slot(par);
       bf16x8 fa[D / 32], fb[D / 32];
-      load_vt_chunk<D>(vt_lds, 0, l32, hi, fa);
+      load_vt_chunk<D>(vt_lds, 0, fa);
       float psum = 0.0f;
       bf16x8 pn[4];
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
         sched_fence();
-        if (c < 3) load_vt_chunk<D>(vt_lds, c + 1, l32, hi, fb);
+        if (c < 3) load_vt_chunk<D>(vt_lds, c + 1, fb);
 #pragma unroll
         for (int db = 0; db < D / 32; ++db) oacc[db] = mfma32(fa[db], pb[c], oacc[db]);
         pn[c] = probs8(s[c >> 1], c & 1, a.scale_log2, m, psum);
         if (c < 3) {  // the next chunk's reads first, then products and softmax interleaved
-          __builtin_amdgcn_sched_group_barrier(0x100, D / 32, 0);
+          __builtin_amdgcn_sched_group_barrier(0x100, D / 16, 0);
 #pragma unroll
           for (int db = 0; db < D / 32; ++db) {
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
@@ -395,8 +386,16 @@ __global__ __launch_bounds__(64 * kWaves, kWavesPerSimd * 4 / kWaves) void fwd_k
       for (int i = 0; i < D / 32; ++i) oacc[i] *= alpha;
     }
     wait_all_memory();
-    __syncthreads();  // V^T of the last tile landed
-    accumulate_pv<D>(v_slot(par), pb, l32, hi, oacc);
+    if (cur * kBN + kBN > N) {  // the value rows past N that this wave copied: zero (0 * inf is not)
+#pragma unroll
+      for (int j = 0; j < CPW; ++j) {
+        const int idx = w + j * kWaves;
+        if (cur * kBN + perm_row(Rows::RPC * idx + lane / Rows::CPR) >= N)
+          *(VC_LDS bf16x8*)((VC_LDS char*)smem + (2 + par) * KT + idx * Rows::GS + 16 * lane) = zero_bf16x8();
+      }
+    }
+    __syncthreads();  // V of the last tile landed
+    accumulate_pv<D>(v_slot(par), pb, oacc);
   }
 
   const float lt = halves_sum(l);

@@ -30,3 +30,26 @@ def test_tile_edges(tokens, head_dim, det):
     for name, a, r in (("O", out["o"], o), ("LSE", out["lse"], lse), ("dQ", out["dq"], dq), ("dK", out["dk"], dk),
                        ("dV", out["dv"], dv)):
         assert_close(name, a, r)
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+def test_infinite_value_in_the_last_row(head_dim):
+    """The value row of key N-1 stands in for the rows past N of the last tile of 64; those
+    have probability 0, which must not turn an infinite value into a NaN: O is infinite in
+    that dim for every query, and finite and equal to the oracle's elsewhere."""
+    import torch
+    import paper_2501_08453_amd as vc
+    w = W.custom(1, 2, head_dim, 0, 1, 1, 131)
+    x = W.make_inputs(w, seed=3)
+    g = {n: to_gpu_bf16(x[n]) for n in ("q", "k", "v")}
+    g["v"][0, 130, 1, 5] = float("inf")
+    o, _ = vc.fwd(g["q"], g["k"], g["v"], vc.desc_for(w))
+    assert bool(torch.isinf(o[0, :, 1, 5]).all())
+    o = bf16_values(o)
+    v = bf16_values(g["v"])
+    v[0, 130, 1, 5] = 0.0
+    ref, _ = ora.attention_forward(bf16_values(g["q"]), bf16_values(g["k"]), v, np.ones((1, 131), dtype=bool),
+                                   ora.default_scale(head_dim))
+    keep = np.ones_like(ref, dtype=bool)
+    keep[0, :, 1, 5] = False
+    assert_close("O", o[keep], ref[keep])
