@@ -154,8 +154,8 @@ vc_status vc_jointattn_fwd_noalloc(const vc_jointattn_desc* desc,
 
 /* Bytes of device workspace the backward needs: per query row fp32 -D and
  * -LSE/c ([B,H,Npad], Npad = N rounded up to 64), the size of three token-major
- * copies (as of the forward's V: one of K, the others' place holds the fp32 dQ
- * accumulator of desc->deterministic = 0), and room for fp32 partial dK, dV (or
+ * copies (as of the forward's V; their place holds the fp32 dQ accumulator of
+ * desc->deterministic = 0), and room for fp32 partial dK, dV (or
  * dQ) of workgroups of 256 rows, as many as and used as in the forward; smaller
  * ones accepted as there. 0 for an invalid descriptor. Host only. */
 size_t vc_jointattn_bwd_workspace_bytes(const vc_jointattn_desc* desc);
@@ -168,8 +168,7 @@ size_t vc_jointattn_bwd_workspace_bytes(const vc_jointattn_desc* desc);
  * no atomics, the result is bitwise reproducible run to run (on devices with a
  * different number of compute units the split of the last round of
  * workgroups, and so the summation order of its rows, differs).
- * desc->deterministic = 0: stage 1 (token-major copy of k only, none when the
- * fused pass carries every key), vc_jointattn_bwd_fused, then stage 3 over the
+ * desc->deterministic = 0: stage 1, vc_jointattn_bwd_fused, then stage 3 over the
  * remaining keys; dk, dv are reproducible run to run, dq only up to the
  * rounding of its fp32 sums. When vc_jointattn_fused_dq_keys(desc) is 0 it
  * runs the deterministic stages instead. */
@@ -180,10 +179,9 @@ vc_status vc_jointattn_bwd(const vc_jointattn_desc* desc,
                            void* dq, void* dk, void* dv,
                            void* workspace, size_t workspace_bytes, void* stream);
 
-/* Backward stage 1: per query row, D_i = sum_d dO_id O_id and LSE_i*log2(e)
- * (fp32, padding rows made inert), the token-major copy of k and, when
- * desc->deterministic = 1, those of q and dout, all into the workspace.
- * Memory-bound. */
+/* Backward stage 1: per query row, D_i = sum_d dO_id O_id and LSE_i / c
+ * (fp32, padding rows made inert), into the workspace. q and k are not read
+ * (earlier versions copied them). Memory-bound. */
 vc_status vc_jointattn_bwd_prepare(const vc_jointattn_desc* desc,
                                    const void* q, const void* k,
                                    const void* o, const float* lse, const void* dout,

@@ -217,13 +217,12 @@ int64_t fwd_tail_wgs(const vc_jointattn_desc* d, int64_t n, size_t have) {
   return tail_wgs(have, tiles_bytes(d, n), fwd_wg_bytes(d->head_dim));
 }
 
-// Backward workspace: -D | -LSE/c | fp32 dQ accumulator (the size of two sets of token
-// tiles, >= 4 bytes per element of dq) | K^T tiles | tail partials.
+// Backward workspace: -D | -LSE/c | fp32 dQ accumulator (in the place of three sets of token
+// tiles, >= 4 bytes per element of dq) | tail partials.
 struct BwdWorkspace {
   float* dd;
   float* nls;
   float* dq_acc;
-  __bf16* kt;
 };
 
 size_t bwd_ws_bytes(const vc_jointattn_desc* d, int64_t n) {
@@ -242,9 +241,9 @@ float* tail_part_of(const vc_jointattn_desc* d, int64_t n, void* ws) {
 
 BwdWorkspace split_bwd_ws(const vc_jointattn_desc* d, int64_t n, void* ws) {
   char* p = static_cast<char*>(ws);
-  const size_t rb = rows_bytes(d, n), tb = tiles_bytes(d, n);
+  const size_t rb = rows_bytes(d, n);
   return BwdWorkspace{reinterpret_cast<float*>(p), reinterpret_cast<float*>(p + rb),
-                      reinterpret_cast<float*>(p + 2 * rb), reinterpret_cast<__bf16*>(p + 2 * rb + 2 * tb)};
+                      reinterpret_cast<float*>(p + 2 * rb)};
 }
 
 // Spatial branch: split of the text key blocks' video query tiles into chunks of about one
@@ -361,7 +360,7 @@ size_t vc_spatialattn_bwd_workspace_bytes(const vc_jointattn_desc* desc) {
 namespace {
 
 vc_status prepare_impl(const vc_jointattn_desc* desc, const void* q, const void* k, const void* o, const float* lse,
-                       const void* dout, void* workspace, size_t workspace_bytes, void* stream, bool key_tiles);
+                       const void* dout, void* workspace, size_t workspace_bytes, void* stream);
 
 // Joint attention (frame_len 0) or the spatial branch (frame_len = tokens per frame).
 vc_status fwd_impl(const vc_jointattn_desc* desc, const void* q, const void* k, const void* v,
@@ -440,18 +439,16 @@ vc_status vc_jointattn_bwd_prepare(const vc_jointattn_desc* desc, const void* q,
   int64_t n = 0;
   const vc_status st = check_desc(desc, &n);
   if (st != VC_OK) return st;
-  return prepare_impl(desc, q, k, o, lse, dout, workspace, workspace_bytes, stream,
-                      desc->deterministic || !all_keys_fused(desc, n));
+  return prepare_impl(desc, q, k, o, lse, dout, workspace, workspace_bytes, stream);
 }
 
 }  // extern "C"
 
 namespace {
 
-// Backward stage 1 and, with `key_tiles`, the token-major copy of k that a dQ pass over key
-// tiles reads (none when every key's dQ share is added in the key-stationary pass).
+// Backward stage 1.
 vc_status prepare_impl(const vc_jointattn_desc* desc, const void* q, const void* k, const void* o, const float* lse,
-                       const void* dout, void* workspace, size_t workspace_bytes, void* stream, bool key_tiles) {
+                       const void* dout, void* workspace, size_t workspace_bytes, void* stream) {
   int64_t n = 0;
   vc_status st = check_desc(desc, &n);
   if (st != VC_OK) return st;
@@ -465,8 +462,6 @@ vc_status prepare_impl(const vc_jointattn_desc* desc, const void* q, const void*
   if (vcja::launch_bwd_prepare(bf(o), lse, bf(dout), w.dd, w.nls, B, H, N, ntiles(n) * vcja::kTileTok, D,
                                scale_of(desc), s) !=
       hipSuccess)
-    return VC_ERR_HIP;
-  if (key_tiles && vcja::launch_token_tiles(bf(k), w.kt, B, H, N, D, s) != hipSuccess)
     return VC_ERR_HIP;
   return VC_OK;
 }
@@ -486,8 +481,7 @@ vc_status dkdv_impl(const vc_jointattn_desc* desc, const void* q, const void* k,
       VC_OK)
     return st;
   if ((st = check_device()) != VC_OK) return st;
-  // The separate stages 2 and 3 belong to the deterministic backward: stage 1 makes the
-  // token-major copy of k that stage 3 reads over all keys only there.
+  // The separate stages 2 and 3 belong to the deterministic backward.
   if (staged && !desc->deterministic) return VC_ERR_UNSUPPORTED;
   const BwdWorkspace w = split_bwd_ws(desc, n, workspace);
   vcja::DkdvArgs a{};
@@ -562,7 +556,6 @@ vc_status dq_impl(const vc_jointattn_desc* desc, const void* q, const void* k, c
   a.k = bf(k);
   a.v = bf(v);
   a.dout = bf(dout);
-  a.kt = w.kt;
   a.nls = w.nls;
   a.dd = w.dd;
   a.text_len = text_len;
@@ -603,14 +596,13 @@ vc_status bwd_impl(const vc_jointattn_desc* desc, const void* q, const void* k, 
   // the others), the spatial branch for every key block (a video query row gets the shares
   // of 16 key blocks at 720p, so the atomics are few); neither past 32-bit dQ offsets.
   if (!desc->deterministic && (spatial ? dq_offsets_fit(desc, n) : fused_dq_blocks(desc, n) > 0)) {
-    if ((st = prepare_impl(desc, q, k, o, lse, dout, workspace, workspace_bytes, stream,
-                           !spatial && !all_keys_fused(desc, n))) != VC_OK ||
+    if ((st = prepare_impl(desc, q, k, o, lse, dout, workspace, workspace_bytes, stream)) != VC_OK ||
         (st = dkdv_impl(desc, q, k, v, dout, text_len, key_mask, dk, dv, workspace, workspace_bytes, stream,
                         spatial, true)) != VC_OK)
       return st;
     return dq_impl(desc, q, k, v, dout, text_len, key_mask, dq, workspace, workspace_bytes, stream, spatial, true);
   }
-  if ((st = prepare_impl(desc, q, k, o, lse, dout, workspace, workspace_bytes, stream, true)) != VC_OK)
+  if ((st = prepare_impl(desc, q, k, o, lse, dout, workspace, workspace_bytes, stream)) != VC_OK)
     return st;
   if ((st = dkdv_impl(desc, q, k, v, dout, text_len, key_mask, dk, dv, workspace, workspace_bytes, stream,
                       spatial)) != VC_OK)

@@ -36,7 +36,11 @@
 //   each wave 32, with Q^T and dO^T of its queries in registers and the lane's
 //   LSE and -D as scalars. It walks over the key tiles like the forward,
 //   computing S^T = K Q^T and dP^T = V dO^T, dS^T, and dQ^T += K^T dS^T with
-//   dS^T taken straight from the accumulator layout (lane column = query).
+//   dS^T taken straight from the accumulator layout (lane column = query) and K^T
+//   from K's own rows by transposing LDS reads; reads, arithmetic and copies are
+//   placed as in the dK/dV walk.
+//   (Over 35% of the keys of 24 heads x 57,856 tokens: 19.4 -> 17.6 ms, and no
+//   token-major copy of K, 128 us.)
 //   This recomputes S and dP once more instead of scattering dQ partial sums
 //   with atomics; the result is bitwise reproducible.
 #include <algorithm>
@@ -662,12 +666,13 @@ __global__ void tail_reduce_kernel(const float* part, __bf16* dk, __bf16* dv, in
 // its per-tile work).
 template <int D, bool KM>
 __global__ __launch_bounds__(64 * kDqWaves, 1) void bwd_dq_kernel(DqArgs a) {
-  constexpr int RT = RowTile<D>::kBytes;      // row-major K or V tile bytes
-  constexpr int RS = RowTile<D>::kStride;
-  constexpr int TT = (int)tile_elems(D) * 2;  // transposed K tile bytes
-  constexpr int STAGE = 2 * RT + TT;          // K | V | K^T
-  constexpr int RCOPIES = RowTile<D>::kCopies;
-  constexpr int TCOPIES = TT / 1024;
+  using Rows = SwzRows<D>;
+  using Reads = SwzReads<D>;
+  constexpr int RT = Rows::bytes(kBN);  // K or V rows of a tile
+  constexpr int STAGE = 2 * RT;         // K | V
+  constexpr int COPIES = kBN / Rows::RPC;
+  constexpr int CPW = COPIES / kDqWaves;  // copies of each per wave and tile
+  static_assert(CPW * kDqWaves == COPIES, "copies of a tile over the waves");
   __shared__ __attribute__((aligned(1024))) char smem[2 * STAGE];
 
   const int tid = threadIdx.x;
@@ -700,14 +705,14 @@ __global__ __launch_bounds__(64 * kDqWaves, 1) void bwd_dq_kernel(DqArgs a) {
   const int qi = rb.r0 + w * 32 + l32;  // this lane's query (accumulator column)
   const int qr = min(qi, rb.r1 - 1);
 
-  // Q^T and dO^T as B operands (dims 16*ks + 8*hi .. +7), LSE*log2e and -D as scalars.
+  // Q^T and dO^T as B operands (dims 16*ks + 8*hi .. +7), -LSE/c and -D as scalars.
   bf16x8 qf[D / 16], dof[D / 16];
 #pragma unroll
   for (int ks = 0; ks < D / 16; ++ks) {
     qf[ks] = *(const bf16x8*)(a.q + base + (size_t)qr * tok + 16 * ks + 8 * hi);
     dof[ks] = *(const bf16x8*)(a.dout + base + (size_t)qr * tok + 16 * ks + 8 * hi);
   }
-  const float nlse2 = a.nls[bh * (size_t)a.ntile * kBN + qr] * a.scale_log2;
+  const float nls = a.nls[bh * (size_t)a.ntile * kBN + qr];
   const float dd = a.dd[bh * (size_t)a.ntile * kBN + qr];
 
   f32x16 dq_acc[D / 32];
@@ -735,33 +740,28 @@ __global__ __launch_bounds__(64 * kDqWaves, 1) void bwd_dq_kernel(DqArgs a) {
     runs.b1 = min(runs.b1, kt0 + a.tail_span);
   }
   auto next_tile = [&](int kt) { return runs.next(kt); };
-  auto issue = [&](int kt, int st) {
-    VC_LDS char* sk = (VC_LDS char*)smem + st * STAGE;
-    for (int idx = w; idx < RCOPIES; idx += kDqWaves) {
-      copy_row_tile<D, true>(a.k + base, tok, kt * kBN, N, sk, idx, lane);
-      copy_row_tile<D, true>(a.v + base, tok, kt * kBN, N, sk + RT, idx, lane);
-    }
-    const __bf16* tsrc = a.kt + (bh * a.ntile + kt) * tile_elems(D);
-    for (int idx = w; idx < TCOPIES; idx += kDqWaves) copy16_to_lds_opaque(tsrc + idx * 512 + lane * 8, sk + 2 * RT + idx * 1024);
+  // This wave's j-th copies of tile kt's K and V rows into stage st (rows past N repeat row
+  // N-1; such keys are masked). K rows, and V rows alike, in perm_row order: K^T comes from
+  // them by transposing reads.
+  const unsigned tok32 = (unsigned)tok;
+  const SwzCopy<D, true> cp(tok32, lane);
+  auto issue_j = [&](int j, bool is_k, int kt, int st) {
+    const int idx = w + j * kDqWaves, first = swz_copy_row<D, true>(kt * kBN, N, idx);
+    copy16_to_lds_opaque((is_k ? a.k : a.v) + base + (size_t)first * tok, cp.offset(first, N, tok32),
+                         (VC_LDS char*)smem + st * STAGE + (is_k ? 0 : RT) + idx * Rows::GS);
   };
-  // The j-th copies of this wave (no-ops past the tile), issued between the score
-  // products of the step's first key block: issued all at the top of the step, eight
-  // waves' copies would hold up the start of every wave's matrix-core work.
-  static_assert((RCOPIES + kDqWaves - 1) / kDqWaves <= D / 32 && (TCOPIES + kDqWaves - 1) / kDqWaves <= D / 32,
-                "every copy of a wave needs a slot among the score products");
-  auto issue_j = [&](int j, int kt, int st) {
-    VC_LDS char* sk = (VC_LDS char*)smem + st * STAGE;
-    const int idx = w + j * kDqWaves;
-    if (idx < RCOPIES) {
-      copy_row_tile<D, true>(a.k + base, tok, kt * kBN, N, sk, idx, lane);
-      copy_row_tile<D, true>(a.v + base, tok, kt * kBN, N, sk + RT, idx, lane);
-    }
-    if (idx < TCOPIES)
-      copy16_to_lds_opaque(a.kt + (bh * a.ntile + kt) * tile_elems(D) + idx * 512 + lane * 8, sk + 2 * RT + idx * 1024);
-  };
+  const int row_base = Reads::row_base(perm_row(l32), hi), tr_base = Reads::tr_base(lane);
 
   int kt = next_tile(kt0);
-  if (kt < a.ntile) issue(kt, 0);
+  if (kt < a.ntile) {
+#pragma unroll
+    for (int j = 0; j < CPW; ++j) {
+      issue_j(j, true, kt, 0);
+      issue_j(j, false, kt, 0);
+    }
+  }
+  wait_all_memory();  // the loads above and the first copies: no later wait stands among copies
+  const float nlse2 = nls * a.scale_log2;
   // Key-mask bytes of each tile loaded a step ahead (waited for at the barrier with the
   // tile's copies), turned into the tile's bits there.
   int kmb = KM && kt < a.ntile ? rule.key_mask_byte(kt, lane) : 1;
@@ -774,9 +774,6 @@ __global__ __launch_bounds__(64 * kDqWaves, 1) void bwd_dq_kernel(DqArgs a) {
     if (KM && kn < a.ntile) kmb = rule.key_mask_byte(kn, lane);
     // a joint tile whose keys are all real (no padding, no text cut): masked by its bits only
     const bool plain_tile = KM && rule.L == 0 && kt * kBN + kBN <= N && (kt * kBN >= a.T || kt * kBN + kBN <= rule.tl);
-    const VC_LDS char* k_lds = (const VC_LDS char*)smem + st * STAGE;
-    const VC_LDS char* v_lds = k_lds + RT;
-    const VC_LDS char* kt_lds = k_lds + 2 * RT;
     const int k0 = kt * kBN;
     bool need_mask;
     if (rule.km || k0 + kBN > N)
@@ -788,52 +785,112 @@ __global__ __launch_bounds__(64 * kDqWaves, 1) void bwd_dq_kernel(DqArgs a) {
     else
       need_mask = !(wave_one_frame && k0 >= wqs && k0 + kBN <= wqs + rule.L);
 
-#pragma unroll
-    for (int kb = 0; kb < kBN / 32; ++kb) {
-      f32x16 s = zero_f32x16(), dp = zero_f32x16();
-#pragma unroll
-      for (int ks = 0; ks < D / 16; ++ks) {
-        const bf16x8 ka = *(const VC_LDS bf16x8*)(k_lds + (kb * 32 + l32) * RS + (2 * ks + hi) * 16);
-        s = mfma32(ka, qf[ks], s);
-        if (kb == 0 && (ks & 1) && kn < a.ntile) issue_j(ks >> 1, kn, st ^ 1);
+    // The two key blocks' products in one stretch of matrix-core ops, every LDS operand read
+    // PF ops ahead, the vector arithmetic of a phase placed between the ops of the next ones:
+    // S0 | dP0, P0 | S1, dS0 | dP1, P1 | dQ += K0^T dS0, dS1 | dQ += K1^T dS1.
+    constexpr int KSN = D / 16;
+    constexpr int NB = D / 32;
+    constexpr int PF = 3;
+    constexpr int EP = 16 / KSN;       // elements per op of a score phase
+    const VC_LDS char* tile = (const VC_LDS char*)smem + st * STAGE;
+    const int kc = kn < a.ntile ? kn : kt;  // next tile's copies (past the last: any tile, never read)
+    bf16x8 f[4 * KSN], g[4 * NB];
+    auto rd = [&](int i) {  // S0, dP0, S1, dP1, then the dQ operands
+      if (i < 4 * KSN) {
+        const int kb = i / (2 * KSN), v = i / KSN % 2;
+        f[i] = *(const VC_LDS bf16x8*)(Reads::row_at(tile + row_base, i % KSN) + v * RT + kb * Rows::bytes(32));
+      } else if (i - 4 * KSN < 4 * NB) {
+        g[i - 4 * KSN] = Reads::tr_operand(tile + tr_base, (i - 4 * KSN) / NB, (i - 4 * KSN) % NB);
       }
+    };
+    f32x16 s[2], dp[2];
+    bf16x8 sb[4];
+    auto form_p = [&](int kb, int r) { s[kb][r] = fast_exp2(fmaf(s[kb][r], a.scale_log2, nlse2)); };
+    auto form_ds = [&](int kb, int r) { dp[kb][r] *= s[kb][r]; };
+    auto operand = [&](const f32x16& x, int half) {
+      bf16x8 y;
 #pragma unroll
-      for (int ks = 0; ks < D / 16; ++ks) {
-        const bf16x8 va = *(const VC_LDS bf16x8*)(v_lds + (kb * 32 + l32) * RS + (2 * ks + hi) * 16);
-        dp = mfma32(va, dof[ks], dp);
+      for (int t = 0; t < 8; ++t) y[t] = (__bf16)x[8 * half + t];
+      return y;
+    };
+#pragma unroll
+    for (int i = 0; i < PF; ++i) rd(i);
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb) {
+      s[kb] = zero_f32x16();
+#pragma unroll
+      for (int i = 0; i < KSN; ++i) {
+        sched_fence();
+        rd(2 * KSN * kb + i + PF);
+        s[kb] = mfma32(f[2 * KSN * kb + i], qf[i], s[kb]);
+        if (kb == 0 && i % 2 == 0 && i / 2 < 2 * CPW) issue_j(i / 4, i / 2 % 2 == 0, kc, st ^ 1);
+        if (kb == 1 && i == 0)
+#pragma unroll
+          for (int e = 0; e < EP; ++e) form_p(0, (KSN - 1) * EP + e);
+        if (kb == 1 && i > 0)
+#pragma unroll
+          for (int e = 0; e < EP; ++e) form_ds(0, (i - 1) * EP + e);
+      }
+      if (kb == 1) {
+#pragma unroll
+        for (int e = 0; e < EP; ++e) form_ds(0, (KSN - 1) * EP + e);
+        sb[0] = operand(dp[0], 0);
+        sb[1] = operand(dp[0], 1);
       }
       // Register r holds key k0 + kb*32 + 8*(r/4) + 4*hi + r%4 of this lane's query.
-      float ds[16];
+      if (need_mask) {
+        sched_fence();
+        if (plain_tile) {  // joint tile of real keys: the key mask's bits alone
+          const unsigned bits = (unsigned)(kbits >> (32 * kb)) >> (4 * hi);
 #pragma unroll
-      for (int r = 0; r < 16; ++r) ds[r] = fast_exp2(fmaf(s[r], a.scale_log2, nlse2));
-      if (need_mask && plain_tile) {  // joint tile of real keys: the key mask's bits alone
-        const unsigned bits = (unsigned)(kbits >> (32 * kb)) >> (4 * hi);
+          for (int r = 0; r < 16; ++r) s[kb][r] = ((bits >> (8 * (r >> 2) + (r & 3))) & 1u) ? s[kb][r] : -INFINITY;
+        } else {  // branch-free per element; the key mask from the tile's bits
 #pragma unroll
-        for (int r = 0; r < 16; ++r) ds[r] = ((bits >> (8 * (r >> 2) + (r & 3))) & 1u) ? ds[r] : 0.0f;
-      } else if (need_mask) {  // branch-free per element; the key mask from the tile's bits
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int key = k0 + kb * 32 + acc_row(r, hi);
-          bool ok = KM ? rule.key_valid_bits(key, k0, kbits) : rule.key_valid(key);
-          if (rule.L) ok = ok & qrange.ok(key, a.T);
-          ds[r] = ok ? ds[r] : 0.0f;
+          for (int r = 0; r < 16; ++r) {
+            const int key = k0 + kb * 32 + acc_row(r, hi);
+            bool ok = rule.key_valid_bits(key, k0, kbits);  // all bits set without a mask
+            if (rule.L) ok = ok & qrange.ok(key, a.T);
+            s[kb][r] = ok ? s[kb][r] : -INFINITY;
+          }
         }
       }
 #pragma unroll
-      for (int r = 0; r < 16; ++r) ds[r] = ds[r] * (dp[r] + dd);
+      for (int r = 0; r < 16; ++r) dp[kb][r] = dd;  // dP - D
 #pragma unroll
-      for (int st2 = 0; st2 < 2; ++st2) {
-        const bf16x8 sb = to_bf16x8(&ds[8 * st2]);
+      for (int i = 0; i < KSN; ++i) {
+        sched_fence();
+        rd(2 * KSN * kb + KSN + i + PF);
+        dp[kb] = mfma32(f[2 * KSN * kb + KSN + i], dof[i], dp[kb]);
+        if (i > 0)
 #pragma unroll
-        for (int db = 0; db < D / 32; ++db) {
-          const int off = ((db * 32 + l32) * kTileRow + kb * 32 + 16 * st2 + 8 * hi) * 2;
-          dq_acc[db] = mfma32(*(const VC_LDS bf16x8*)(kt_lds + off), sb, dq_acc[db]);
-        }
+          for (int e = 0; e < EP; ++e) form_p(kb, (i - 1) * EP + e);
       }
     }
+    constexpr int ED = 16 / (2 * NB);  // elements per op of a dQ phase
+#pragma unroll
+    for (int i = 0; i < 4 * NB; ++i) {
+      sched_fence();
+      rd(4 * KSN + i + PF);
+      dq_acc[i % NB] = mfma32(g[i], sb[i / NB], dq_acc[i % NB]);
+      if (i == 0)
+#pragma unroll
+        for (int e = 0; e < EP; ++e) form_p(1, (KSN - 1) * EP + e);
+      else if (i < 2 * NB)
+#pragma unroll
+        for (int e = 0; e < ED; ++e) form_ds(1, (i - 1) * ED + e);
+      if (i == 2 * NB - 1) {
+#pragma unroll
+        for (int e = 0; e < ED; ++e) form_ds(1, (2 * NB - 1) * ED + e);
+        sb[2] = operand(dp[1], 0);
+        sb[3] = operand(dp[1], 1);
+      }
+    }
+    sched_fence();
     st ^= 1;
     kt = kn;
   }
+
+  wait_all_memory();  // no copy outlives the workgroup
 
   if (tail) {  // partial dQ of this lane's query row
     float* pq = a.tail_part + (((size_t)ti.slot * a.tail_chunks + ti.chunk) * kDqBM + (qi - rb.r0)) * D;
@@ -884,22 +941,6 @@ __global__ void tail_reduce_dq_kernel(const float* part, __bf16* dq, int B, int 
   *(bf16x4*)(dq + off) = bf16x4{(__bf16)s[0], (__bf16)s[1], (__bf16)s[2], (__bf16)s[3]};
 }
 
-// dq = bf16(scale * acc), four elements per thread.
-__global__ void dq_from_acc_kernel(const float* acc, __bf16* dq, size_t n4, float scale) {
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n4) return;
-  const f32x4 x = ((const f32x4*)acc)[i];
-  ((bf16x4*)dq)[i] = bf16x4{(__bf16)(x[0] * scale), (__bf16)(x[1] * scale), (__bf16)(x[2] * scale),
-                            (__bf16)(x[3] * scale)};
-}
-
-// Fused dQ: zeroes the fp32 accumulator (a kernel, not a memset, so that a captured graph
-// replays it like any other node). n4 = elements / 4.
-__global__ void zero_f32_kernel(float* x, size_t n4) {
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n4) ((f32x4*)x)[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-}
-
 }  // namespace
 
 hipError_t launch_bwd_prepare(const __bf16* o, const float* lse, const __bf16* dout, float* dd, float* nls, int B,
@@ -921,9 +962,10 @@ hipError_t launch_bwd_dkdv(const DkdvArgs& a, int head_dim, hipStream_t s) {
   dim3 grid = spatial ? dim3(nblk + (split ? (a.text_chunks - 1) * a.text_blocks : 0), a.H, a.B)
                       : dim3(nblk * a.H * a.B + a.tail_blocks * (a.tail_chunks - 1));
   const bool fused = a.dq_acc != nullptr;
-  const size_t dq4 = (size_t)a.B * a.N * a.H * head_dim / 4;
-  const dim3 egrid((unsigned)((dq4 + 255) / 256));
-  if (fused) hipLaunchKernelGGL(zero_f32_kernel, egrid, dim3(256), 0, s, a.dq_acc, dq4);
+  if (fused) {
+    const hipError_t e = launch_zero_f32(a.dq_acc, (size_t)a.B * a.N * a.H * head_dim, s);
+    if (e != hipSuccess) return e;
+  }
   if (head_dim == 128 && spatial && fused)
     hipLaunchKernelGGL((bwd_dkdv_kernel<128, true, true>), grid, dim3(64 * kDkdvWaves), 0, s, a);
   else if (head_dim == 128 && spatial)
@@ -962,12 +1004,6 @@ hipError_t launch_bwd_dkdv(const DkdvArgs& a, int head_dim, hipStream_t s) {
       hipLaunchKernelGGL(text_reduce_kernel<64>, rgrid, dim3(256), 0, s, a.text_part, a.dk, a.dv, a.B, a.H, a.N,
                          rows, nrow, a.text_chunks);
   }
-  return hipGetLastError();
-}
-
-hipError_t launch_dq_from_acc(const float* acc, __bf16* dq, size_t n, float scale, hipStream_t s) {
-  const size_t n4 = n / 4;
-  if (n4) hipLaunchKernelGGL(dq_from_acc_kernel, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s, acc, dq, n4, scale);
   return hipGetLastError();
 }
 

@@ -98,19 +98,6 @@ __device__ __forceinline__ bf16x4 lds_read_tr(const VC_LDS void* p) {
   return __builtin_bit_cast(bf16x4, v);
 }
 
-// Row-major bf16 tile of 64 token rows x D in LDS with one 16-byte pad chunk per row:
-// row stride D*2 + 16 bytes, so the 16 rows read by one quarter-wave at a common column
-// fall on distinct banks, and every k-step of an operand read is an immediate offset
-// from one per-lane base address.
-template <int D>
-struct RowTile {
-  static constexpr int kChunks = D / 8 + 1;             // 16-byte chunks per row, pad included
-  static constexpr int kStride = kChunks * 16;          // bytes per row
-  static constexpr int kBytes = kTileTok * kStride;     // bytes per tile
-  static constexpr int kCopies = kTileTok * kChunks / 64;  // 1 KiB wave copies per tile
-  static_assert(kTileTok * kChunks % 64 == 0, "tile must be whole wave copies");
-};
-
 // Row order of a permuted row tile: token 16g + 4m + i of the tile sits in LDS row
 // 16g + 4i + m (a 4x4 transpose inside each run of 16; its own inverse). Four consecutive
 // tokens then lie 4 rows apart, so that a transposing read of them (4 rows x 64 bytes per
@@ -124,8 +111,9 @@ __host__ __device__ constexpr int perm_row(int t) { return (t & ~15) | ((t & 3) 
 // distinct banks the 16 rows one quarter-wave reads at a common chunk and, with rows in
 // perm_row order, the 4 rows x 64 bytes of a half-wave's transposing read. As a copy's rows
 // start a fixed number of tokens apart, its lanes' offsets from the copy's first row are
-// the same for every copy and tile: the padded RowTile, whose copies cover 3.8 rows each,
-// needs a division and a 64-bit address per lane and copy (about 20 vector instructions).
+// the same for every copy and tile (rows padded to 17 chunks, whose copies cover 3.8 rows
+// each, need a division and a 64-bit address per lane and copy: about 20 vector
+// instructions).
 template <int D>
 struct SwzRows {
   static constexpr int CPR = D / 8;                    // 16-byte chunks per row
@@ -198,37 +186,6 @@ struct SwzReads {
   }
 };
 
-// Issues wave copy `idx` of a row tile: rows row0 .. row0+63 of the [B, N, H, D] tensor
-// slice at src (row r at src + r*tok), rows clamped to N-1. The pad chunk of each row
-// repeats the row's last chunk. PERM: the tile's rows in perm_row order.
-template <int D, bool OPAQUE = false, bool PERM = false>
-__device__ __forceinline__ void copy_row_tile(const __bf16* src, size_t tok, int row0, int N, VC_LDS char* dst,
-                                              int idx, int lane) {
-  constexpr int CH = RowTile<D>::kChunks;
-  const int lin = idx * 64 + lane;
-  const int r = lin / CH;
-  const int c = min(lin - r * CH, CH - 2);
-  const __bf16* g = src + (size_t)min(row0 + (PERM ? perm_row(r) : r), N - 1) * tok + c * 8;
-  if constexpr (OPAQUE)
-    copy16_to_lds_opaque(g, dst + idx * 1024);
-  else
-    copy16_to_lds(g, dst + idx * 1024);
-}
-
-// Scheduling hint for the basic block it ends: issue `lead` LDS reads, then `n` times
-// {1 matrix-core op, 1 LDS read, v vector-ALU ops}, so that independent vector work
-// (softmax, elementwise gradients) executes while the matrix core is busy.
-template <int lead, int n, int v>
-__device__ __forceinline__ void interleave_mfma_valu() {
-  __builtin_amdgcn_sched_group_barrier(0x100, lead, 0);
-#pragma unroll
-  for (int i = 0; i < n; ++i) {
-    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-    __builtin_amdgcn_sched_group_barrier(0x002, v, 0);
-  }
-}
-
 // Bits of a tile's key mask from the lanes' bytes (AttendRule::key_mask_byte): bit i = the
 // byte of lane i is non-zero. Wave-uniform.
 __device__ __forceinline__ unsigned long long key_mask_bits(int byte) { return __ballot(byte != 0); }
@@ -243,19 +200,10 @@ __device__ __forceinline__ float halves_sum(float x) { return x + swap_halves(x)
 // Keeps the compiler from moving any instruction across this point.
 __device__ __forceinline__ void sched_fence() { __builtin_amdgcn_sched_barrier(0); }
 
-// Transposed token tiles ("token-major" copies). A [B, N, H, D] tensor X is also kept as
-// blocked tiles XT[b][h][tile][d][kTileRow] of kTileTok tokens: row d of a tile holds
-// X[tile*64 + tok][d] for the 64 tokens, followed by 8 padding elements (so that the 32
-// rows read by one MFMA operand fall on distinct LDS banks). Inside each run of 16 tokens
-// the second and third groups of 4 are swapped, so that the 8 tokens a lane supplies to
-// one 32x32x16 MFMA step - tokens 16s + 8*(t/4) + 4*hi + t%4, t = 0..7, the order in
-// which an accumulator column holds them - are 8 consecutive elements (one 16-byte read).
-constexpr int kTileRow = kTileTok + 8;  // elements per transposed tile row
+// Elements of a token-major tile (kTileTok tokens as D rows of 64 + 8): the unit in which the
+// workspaces are sized, from versions that kept transposed copies there.
+constexpr int kTileRow = kTileTok + 8;
 __host__ __device__ constexpr size_t tile_elems(int d) { return (size_t)d * kTileRow; }
-// Position of token t (0..63) inside a transposed tile row.
-__host__ __device__ constexpr int tok_pos(int t) {
-  return (t & ~15) | (((t >> 2) & 3) == 1 ? 8 : ((t >> 2) & 3) == 2 ? 4 : ((t >> 2) & 3) * 4) | (t & 3);
-}
 
 // Joint attention runs a 1-D grid of items (row block, head, sample), row block fastest.
 // The last `tail_items` items, those of the last, partial round of dispatch, are replaced by
@@ -449,7 +397,6 @@ struct DqArgs {
   const __bf16* k;
   const __bf16* v;
   const __bf16* dout;
-  const __bf16* kt;     // K as transposed token tiles
   const float* nls;
   const float* dd;
   const int32_t* text_len;
@@ -501,8 +448,6 @@ struct TemporalArgs {
 
 // Host-side launchers (defined in the .hip kernel files).
 namespace vcja {
-// Writes the transposed token tiles of x ([B, N, H, D]) into xt.
-hipError_t launch_token_tiles(const __bf16* x, __bf16* xt, int B, int H, int N, int head_dim, hipStream_t s);
 hipError_t launch_fwd(const FwdArgs& a, int head_dim, hipStream_t s);
 hipError_t launch_bwd_prepare(const __bf16* o, const float* lse, const __bf16* dout, float* dd, float* nls, int B,
                               int H, int N, int Npad, int head_dim, float scale, hipStream_t s);
@@ -510,6 +455,7 @@ hipError_t launch_bwd_dkdv(const DkdvArgs& a, int head_dim, hipStream_t s);
 hipError_t launch_bwd_dq(const DqArgs& a, int head_dim, hipStream_t s);
 // dq = bf16(scale * acc) over n elements (a fused backward whose key blocks all added their
 // dQ share to the fp32 accumulator acc, [B, N, H, D] like dq). n a multiple of 4.
+hipError_t launch_zero_f32(float* x, size_t n, hipStream_t s);  // n a multiple of 4
 hipError_t launch_dq_from_acc(const float* acc, __bf16* dq, size_t n, float scale, hipStream_t s);
 hipError_t launch_temporal_fwd(const TemporalArgs& a, int head_dim, hipStream_t s);
 hipError_t launch_temporal_bwd(const TemporalArgs& a, int head_dim, hipStream_t s);

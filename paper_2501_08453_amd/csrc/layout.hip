@@ -1,51 +1,36 @@
-// Transposed token tiles (layout described in common.hpp): a memory-bound
-// reformatting pass that lets the attention kernels fetch every operand whose
-// contraction runs over tokens (V^T in the forward; Q^T, dO^T and K^T in the
-// backward) with plain 16-byte LDS reads instead of transposing reads.
+// The backward's fp32 dQ accumulator: clearing it, and turning it into dQ. Memory-bound.
 #include "common.hpp"
 
 namespace vcja {
 namespace {
 
-template <int D>
-__global__ __launch_bounds__(256) void token_tiles_kernel(const __bf16* __restrict__ x, __bf16* __restrict__ xt,
-                                                          int H, int N, int ntile) {
-  constexpr int CPR = D / 8;       // 16-byte chunks per token row
-  constexpr int RS = D + 8;        // LDS row stride (elements)
-  constexpr int OCH = kTileRow / 8;  // 16-byte chunks per output row (9)
-  __shared__ __attribute__((aligned(16))) __bf16 buf[kTileTok * RS];
-  const int tile = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-  const size_t tok = (size_t)H * D;
-  const __bf16* src = x + (size_t)b * N * tok + (size_t)h * D;
-  for (int c = threadIdx.x; c < kTileTok * CPR; c += 256) {
-    const int t = c / CPR, col = (c % CPR) * 8;
-    const int n = tile * kTileTok + t;
-    bf16x8 v = zero_bf16x8();
-    if (n < N) v = *(const bf16x8*)(src + (size_t)n * tok + col);
-    *(bf16x8*)&buf[t * RS + col] = v;
-  }
-  __syncthreads();
-  __bf16* dst = xt + (((size_t)b * H + h) * ntile + tile) * tile_elems(D);
-  for (int c = threadIdx.x; c < D * OCH; c += 256) {
-    const int d = c / OCH, pc = c % OCH;
-    bf16x8 v = zero_bf16x8();
-    if (pc < kTileTok / 8) {
-#pragma unroll
-      for (int i = 0; i < 8; ++i) v[i] = buf[tok_pos(pc * 8 + i) * RS + d];  // tok_pos is an involution
-    }
-    *(bf16x8*)(dst + (size_t)d * kTileRow + pc * 8) = v;
-  }
+// dq = bf16(scale * acc), four elements per thread.
+__global__ void dq_from_acc_kernel(const float* acc, __bf16* dq, size_t n4, float scale) {
+  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n4) return;
+  const f32x4 x = ((const f32x4*)acc)[i];
+  ((bf16x4*)dq)[i] = bf16x4{(__bf16)(x[0] * scale), (__bf16)(x[1] * scale), (__bf16)(x[2] * scale),
+                            (__bf16)(x[3] * scale)};
+}
+
+// Fused dQ: zeroes the fp32 accumulator (a kernel, not a memset, so that a captured graph
+// replays it like any other node). n4 = elements / 4.
+__global__ void zero_f32_kernel(float* x, size_t n4) {
+  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n4) ((f32x4*)x)[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 }
 
 }  // namespace
 
-hipError_t launch_token_tiles(const __bf16* x, __bf16* xt, int B, int H, int N, int head_dim, hipStream_t s) {
-  const int ntile = (N + kTileTok - 1) / kTileTok;
-  dim3 grid(ntile, H, B);
-  if (head_dim == 128)
-    hipLaunchKernelGGL(token_tiles_kernel<128>, grid, dim3(256), 0, s, x, xt, H, N, ntile);
-  else
-    hipLaunchKernelGGL(token_tiles_kernel<64>, grid, dim3(256), 0, s, x, xt, H, N, ntile);
+hipError_t launch_zero_f32(float* x, size_t n, hipStream_t s) {
+  const size_t n4 = n / 4;
+  if (n4) hipLaunchKernelGGL(zero_f32_kernel, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s, x, n4);
+  return hipGetLastError();
+}
+
+hipError_t launch_dq_from_acc(const float* acc, __bf16* dq, size_t n, float scale, hipStream_t s) {
+  const size_t n4 = n / 4;
+  if (n4) hipLaunchKernelGGL(dq_from_acc_kernel, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s, acc, dq, n4, scale);
   return hipGetLastError();
 }
 
