@@ -360,7 +360,7 @@ size_t vc_spatialattn_bwd_workspace_bytes(const vc_jointattn_desc* desc) {
 namespace {
 
 vc_status prepare_impl(const vc_jointattn_desc* desc, const void* q, const void* k, const void* o, const float* lse,
-                       const void* dout, void* workspace, size_t workspace_bytes, void* stream);
+                       const void* dout, void* workspace, size_t workspace_bytes, void* stream, bool zero_acc = false);
 
 // Joint attention (frame_len 0) or the spatial branch (frame_len = tokens per frame).
 vc_status fwd_impl(const vc_jointattn_desc* desc, const void* q, const void* k, const void* v,
@@ -396,10 +396,6 @@ vc_status fwd_impl(const vc_jointattn_desc* desc, const void* q, const void* k, 
   a.tail_blocks = tp.items;
   a.tail_chunks = tp.chunks;
   a.tail_span = tp.span;
-  // Spatial branch: text rows are not queries; their o and lse are written here.
-  if (spatial && vcja::launch_text_rows(a.o, nullptr, nullptr, lse, a.B, a.H, a.N, a.T, desc->head_dim,
-                                        as_stream(stream)) != hipSuccess)
-    return VC_ERR_HIP;
   return vcja::launch_fwd(a, desc->head_dim, as_stream(stream)) == hipSuccess ? VC_OK : VC_ERR_HIP;
 }
 
@@ -446,9 +442,9 @@ vc_status vc_jointattn_bwd_prepare(const vc_jointattn_desc* desc, const void* q,
 
 namespace {
 
-// Backward stage 1.
+// Backward stage 1; with zero_acc it also clears the fused pass's dQ accumulator.
 vc_status prepare_impl(const vc_jointattn_desc* desc, const void* q, const void* k, const void* o, const float* lse,
-                       const void* dout, void* workspace, size_t workspace_bytes, void* stream) {
+                       const void* dout, void* workspace, size_t workspace_bytes, void* stream, bool zero_acc) {
   int64_t n = 0;
   vc_status st = check_desc(desc, &n);
   if (st != VC_OK) return st;
@@ -459,9 +455,8 @@ vc_status prepare_impl(const vc_jointattn_desc* desc, const void* q, const void*
   const BwdWorkspace w = split_bwd_ws(desc, n, workspace);
   const int B = desc->batch, H = desc->heads, D = desc->head_dim, N = (int)n;
   hipStream_t s = as_stream(stream);
-  if (vcja::launch_bwd_prepare(bf(o), lse, bf(dout), w.dd, w.nls, B, H, N, ntiles(n) * vcja::kTileTok, D,
-                               scale_of(desc), s) !=
-      hipSuccess)
+  if (vcja::launch_bwd_prepare(bf(o), lse, bf(dout), w.dd, w.nls, B, H, N, ntiles(n) * vcja::kTileTok, D, scale_of(desc),
+                               zero_acc ? w.dq_acc : nullptr, s) != hipSuccess)
     return VC_ERR_HIP;
   return VC_OK;
 }
@@ -469,7 +464,7 @@ vc_status prepare_impl(const vc_jointattn_desc* desc, const void* q, const void*
 vc_status dkdv_impl(const vc_jointattn_desc* desc, const void* q, const void* k, const void* v, const void* dout,
                     const int32_t* text_len, const uint8_t* key_mask, void* dk, void* dv, void* workspace,
                     size_t workspace_bytes, void* stream, bool spatial, bool fused = false,
-                    bool staged = false) {
+                    bool staged = false, bool zero_acc = true) {
   int64_t n = 0;
   vc_status st = check_desc(desc, &n);
   if (st != VC_OK) return st;
@@ -508,6 +503,7 @@ vc_status dkdv_impl(const vc_jointattn_desc* desc, const void* q, const void* k,
   a.dk = static_cast<__bf16*>(dk);
   a.dv = static_cast<__bf16*>(dv);
   a.dq_acc = fused ? w.dq_acc : nullptr;
+  a.zero_acc = zero_acc;
   a.dq_blocks = !fused ? 0 : spatial ? std::numeric_limits<int>::max() : fused_dq_blocks(desc, n);
   a.B = desc->batch;
   a.H = desc->heads;
@@ -537,17 +533,13 @@ vc_status dq_impl(const vc_jointattn_desc* desc, const void* q, const void* k, c
   // share, plus the accumulator the others filled; when every block added its share, the
   // accumulator alone, scaled and rounded.
   if (fused) {
-    if (spatial || all_keys_fused(desc, n)) {
-      hipStream_t s = as_stream(stream);
-      if (vcja::launch_dq_from_acc(w.dq_acc, static_cast<__bf16*>(dq),
-                                   (size_t)desc->batch * n * desc->heads * desc->head_dim, scale_of(desc),
-                                   s) != hipSuccess)
-        return VC_ERR_HIP;
-      // Spatial branch: text rows are not queries; their dq is zero.
-      if (spatial && vcja::launch_text_rows(static_cast<__bf16*>(dq), nullptr, nullptr, nullptr, desc->batch,
-                                            desc->heads, (int)n, desc->text_slot, desc->head_dim, s) != hipSuccess)
-        return VC_ERR_HIP;
-      return VC_OK;
+    if (spatial || all_keys_fused(desc, n)) {  // spatial: text rows are not queries, their dq is zero
+      const size_t tok = (size_t)desc->heads * desc->head_dim;
+      return vcja::launch_dq_from_acc(w.dq_acc, static_cast<__bf16*>(dq), desc->batch, n * tok,
+                                      spatial ? desc->text_slot * tok : 0, scale_of(desc),
+                                      as_stream(stream)) == hipSuccess
+                 ? VC_OK
+                 : VC_ERR_HIP;
     }
     a.kt_min = fused_dq_blocks(desc, n) * (vcja::kDkdvKeys / vcja::kTileTok);
     a.dq_acc = w.dq_acc;
@@ -576,10 +568,6 @@ vc_status dq_impl(const vc_jointattn_desc* desc, const void* q, const void* k, c
   a.frame_len = spatial ? desc->grid_h * desc->grid_w : 0;
   a.scale = scale_of(desc);
   a.scale_log2 = a.scale * vcja::kLog2e;
-  // Spatial branch: text rows are not queries; their dq is zero.
-  if (spatial && vcja::launch_text_rows(a.dq, nullptr, nullptr, nullptr, a.B, a.H, a.N, a.T, desc->head_dim,
-                                        as_stream(stream)) != hipSuccess)
-    return VC_ERR_HIP;
   return vcja::launch_bwd_dq(a, desc->head_dim, as_stream(stream)) == hipSuccess ? VC_OK : VC_ERR_HIP;
 }
 
@@ -596,9 +584,9 @@ vc_status bwd_impl(const vc_jointattn_desc* desc, const void* q, const void* k, 
   // the others), the spatial branch for every key block (a video query row gets the shares
   // of 16 key blocks at 720p, so the atomics are few); neither past 32-bit dQ offsets.
   if (!desc->deterministic && (spatial ? dq_offsets_fit(desc, n) : fused_dq_blocks(desc, n) > 0)) {
-    if ((st = prepare_impl(desc, q, k, o, lse, dout, workspace, workspace_bytes, stream)) != VC_OK ||
+    if ((st = prepare_impl(desc, q, k, o, lse, dout, workspace, workspace_bytes, stream, true)) != VC_OK ||
         (st = dkdv_impl(desc, q, k, v, dout, text_len, key_mask, dk, dv, workspace, workspace_bytes, stream,
-                        spatial, true)) != VC_OK)
+                        spatial, true, false, false)) != VC_OK)
       return st;
     return dq_impl(desc, q, k, v, dout, text_len, key_mask, dq, workspace, workspace_bytes, stream, spatial, true);
   }
@@ -678,12 +666,6 @@ vc_status temporal_fwd_impl(const vc_jointattn_desc* desc, const void* q, const 
   a.sum_b = bf(o_spatial);
   a.sum_out = static_cast<__bf16*>(out);
   hipStream_t s = as_stream(stream);
-  if (vcja::launch_text_rows(a.o, nullptr, nullptr, lse, a.B, a.H, a.N, a.T, desc->head_dim, s) != hipSuccess)
-    return VC_ERR_HIP;
-  // text rows of the sum: this branch contributes zero there
-  if (out && vcja::launch_branch_sum(a.sum_a, a.sum_b, nullptr, a.sum_out, a.B, a.N, a.T, a.H * desc->head_dim, s) !=
-                 hipSuccess)
-    return VC_ERR_HIP;
   const hipError_t e = desc->frames > vcja::kMaxTemporalFramesShort
                           ? vcja::launch_temporal_long_fwd(a, desc->head_dim, device_cus(), s)
                           : vcja::launch_temporal_fwd(a, desc->head_dim, s);
@@ -751,8 +733,6 @@ vc_status vc_temporalattn_bwd(const vc_jointattn_desc* desc, const void* q, cons
   a.dk = static_cast<__bf16*>(dk);
   a.dv = static_cast<__bf16*>(dv);
   hipStream_t s = as_stream(stream);
-  if (vcja::launch_text_rows(a.o, a.dk, a.dv, nullptr, a.B, a.H, a.N, a.T, desc->head_dim, s) != hipSuccess)
-    return VC_ERR_HIP;
   // -D and LSE*log2(e) are formed inside the kernels from o and lse: no workspace.
   a.lse = const_cast<float*>(lse);
   a.o_in = bf(o);

@@ -64,7 +64,8 @@ __global__ __launch_bounds__(256) void bwd_prepare_kernel(const __bf16* __restri
                                                           const float* __restrict__ lse,
                                                           const __bf16* __restrict__ dout,
                                                           float* __restrict__ dd, float* __restrict__ nls, int B,
-                                                          int H, int N, int Npad, float inv_scale) {
+                                                          int H, int N, int Npad, float inv_scale,
+                                                          float* __restrict__ zero_acc) {
   constexpr int CPR = D / 8;  // 16-byte chunks per (token, head) row
   const size_t gid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   const size_t rows = (size_t)B * N * H;
@@ -76,6 +77,10 @@ __global__ __launch_bounds__(256) void bwd_prepare_kernel(const __bf16* __restri
     const bf16x8 y = *(const bf16x8*)(dout + row * D + chunk * 8);
 #pragma unroll
     for (int e = 0; e < 8; ++e) sum = fmaf((float)x[e], (float)y[e], sum);
+    if (zero_acc) {  // the dQ accumulator of a fused pass, cleared on the way
+      *(f32x4*)(zero_acc + row * D + chunk * 8) = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+      *(f32x4*)(zero_acc + row * D + chunk * 8 + 4) = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    }
   }
 #pragma unroll
   for (int off = 1; off < CPR; off <<= 1) sum += __shfl_xor(sum, off, 64);
@@ -694,13 +699,15 @@ __global__ __launch_bounds__(64 * kDqWaves, 1) void bwd_dq_kernel(DqArgs a) {
     h = ti.h;
     b = ti.b;
   }
+  if (a.frame_len)  // text rows are not queries of the spatial branch
+    write_text_rows<D>(TextRows{a.dq, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr}, a.B, a.H, a.N, a.T, tid,
+                       blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z), gridDim.x * gridDim.y * gridDim.z);
   const bool tail = ti.chunk >= 0;
   const int N = a.N;
   const size_t tok = (size_t)a.H * D;
   const size_t base = (size_t)b * N * tok + (size_t)h * D;
   const size_t bh = (size_t)b * a.H + h;
-  // This workgroup's queries (spatial branch: inside one frame; text rows of dQ are written
-  // by the caller's text-rows pass).
+  // This workgroup's queries (spatial branch: inside one frame).
   const RowBlock rb = row_block(gx, N, a.T, a.frame_len, kDqBM, false);
   const int qi = rb.r0 + w * 32 + l32;  // this lane's query (accumulator column)
   const int qr = min(qi, rb.r1 - 1);
@@ -944,13 +951,15 @@ __global__ void tail_reduce_dq_kernel(const float* part, __bf16* dq, int B, int 
 }  // namespace
 
 hipError_t launch_bwd_prepare(const __bf16* o, const float* lse, const __bf16* dout, float* dd, float* nls, int B,
-                              int H, int N, int Npad, int head_dim, float scale, hipStream_t s) {
+                              int H, int N, int Npad, int head_dim, float scale, float* zero_acc, hipStream_t s) {
   const size_t threads = std::max((size_t)B * N * H * (head_dim / 8), (size_t)B * H * (Npad - N));
   dim3 grid((unsigned)((threads + 255) / 256));
   if (head_dim == 128)
-    hipLaunchKernelGGL(bwd_prepare_kernel<128>, grid, dim3(256), 0, s, o, lse, dout, dd, nls, B, H, N, Npad, 1.0f / scale);
+    hipLaunchKernelGGL(bwd_prepare_kernel<128>, grid, dim3(256), 0, s, o, lse, dout, dd, nls, B, H, N, Npad, 1.0f / scale,
+                       zero_acc);
   else
-    hipLaunchKernelGGL(bwd_prepare_kernel<64>, grid, dim3(256), 0, s, o, lse, dout, dd, nls, B, H, N, Npad, 1.0f / scale);
+    hipLaunchKernelGGL(bwd_prepare_kernel<64>, grid, dim3(256), 0, s, o, lse, dout, dd, nls, B, H, N, Npad, 1.0f / scale,
+                       zero_acc);
   return hipGetLastError();
 }
 
@@ -962,7 +971,7 @@ hipError_t launch_bwd_dkdv(const DkdvArgs& a, int head_dim, hipStream_t s) {
   dim3 grid = spatial ? dim3(nblk + (split ? (a.text_chunks - 1) * a.text_blocks : 0), a.H, a.B)
                       : dim3(nblk * a.H * a.B + a.tail_blocks * (a.tail_chunks - 1));
   const bool fused = a.dq_acc != nullptr;
-  if (fused) {
+  if (fused && a.zero_acc) {
     const hipError_t e = launch_zero_f32(a.dq_acc, (size_t)a.B * a.N * a.H * head_dim, s);
     if (e != hipSuccess) return e;
   }

@@ -200,6 +200,39 @@ __device__ __forceinline__ float halves_sum(float x) { return x + swap_halves(x)
 // Keeps the compiler from moving any instruction across this point.
 __device__ __forceinline__ void sched_fence() { __builtin_amdgcn_sched_barrier(0); }
 
+// Rows [0, T) of up to three [B, N, H, D] tensors set to zero and, if lse is given, their LSE
+// ([B, H, N]) to -inf: the text rows of the branches in which text is no query, written by
+// the first threads of the branch's own grid. (A launch of their own took 5 us, a quarter of
+// a small temporal forward: 20.2 -> 17.1 us a call.) Every workgroup calls it. With `sum`, rows of sum = (sum_a + sum_b) too (fp32, rounded once; a
+// NULL input counts as zero).
+struct TextRows {
+  __bf16 *x0, *x1, *x2;
+  float* lse;
+  const __bf16 *sum_a, *sum_b;
+  __bf16* sum;
+};
+template <int D>
+__device__ __forceinline__ void write_text_rows(const TextRows& t, int B, int H, int N, int T, int tid, int wg, int wgs) {
+  constexpr int CPR = D / 8;  // 16-byte chunks per row
+  const size_t per = (size_t)T * H * CPR;
+  for (size_t i = (size_t)wg * blockDim.x + tid; i < B * per; i += (size_t)wgs * blockDim.x) {
+    const size_t b = i / per, r = i % per;  // rows [0, T) of a sample are contiguous
+    const size_t off = b * N * H * D + r * 8;
+    const bf16x8 z = zero_bf16x8();
+    if (t.x0) *(bf16x8*)(t.x0 + off) = z;
+    if (t.x1) *(bf16x8*)(t.x1 + off) = z;
+    if (t.x2) *(bf16x8*)(t.x2 + off) = z;
+    if (t.lse && r % CPR == 0) t.lse[(b * H + (r / CPR) % H) * N + r / (CPR * H)] = -INFINITY;
+    if (t.sum) {
+      float x[8] = {};
+      const bf16x8 a = t.sum_a ? *(const bf16x8*)(t.sum_a + off) : z, c = t.sum_b ? *(const bf16x8*)(t.sum_b + off) : z;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) x[e] = (x[e] + (float)a[e]) + (float)c[e];
+      *(bf16x8*)(t.sum + off) = to_bf16x8(x);
+    }
+  }
+}
+
 // Elements of a token-major tile (kTileTok tokens as D rows of 64 + 8): the unit in which the
 // workspaces are sized, from versions that kept transposed copies there.
 constexpr int kTileRow = kTileTok + 8;
@@ -387,6 +420,7 @@ struct DkdvArgs {
   // the share of the other keys.
   float* dq_acc;
   int dq_blocks;
+  bool zero_acc;  // clear dq_acc first (stage 1 has done so otherwise)
 };
 
 constexpr int kDkdvKeys = 256;  // keys per dK/dV workgroup
@@ -450,13 +484,15 @@ struct TemporalArgs {
 namespace vcja {
 hipError_t launch_fwd(const FwdArgs& a, int head_dim, hipStream_t s);
 hipError_t launch_bwd_prepare(const __bf16* o, const float* lse, const __bf16* dout, float* dd, float* nls, int B,
-                              int H, int N, int Npad, int head_dim, float scale, hipStream_t s);
+                              int H, int N, int Npad, int head_dim, float scale, float* zero_acc, hipStream_t s);
 hipError_t launch_bwd_dkdv(const DkdvArgs& a, int head_dim, hipStream_t s);
 hipError_t launch_bwd_dq(const DqArgs& a, int head_dim, hipStream_t s);
 // dq = bf16(scale * acc) over n elements (a fused backward whose key blocks all added their
 // dQ share to the fp32 accumulator acc, [B, N, H, D] like dq). n a multiple of 4.
+// The first `zero` of each sample's elements are written as zero instead.
 hipError_t launch_zero_f32(float* x, size_t n, hipStream_t s);  // n a multiple of 4
-hipError_t launch_dq_from_acc(const float* acc, __bf16* dq, size_t n, float scale, hipStream_t s);
+hipError_t launch_dq_from_acc(const float* acc, __bf16* dq, int B, size_t per_sample, size_t zero, float scale,
+                              hipStream_t s);
 hipError_t launch_temporal_fwd(const TemporalArgs& a, int head_dim, hipStream_t s);
 hipError_t launch_temporal_bwd(const TemporalArgs& a, int head_dim, hipStream_t s);
 // Long clips (F > 32): persistent grid of at most `cus` workgroups. The backwards (both
@@ -468,8 +504,4 @@ hipError_t launch_temporal_long_bwd(const TemporalArgs& a, int head_dim, int cus
 // counts as zero; out may be one of the inputs.
 hipError_t launch_branch_sum(const __bf16* a, const __bf16* b, const __bf16* c, __bf16* out, int B, int N, int rows,
                              int row_elems, hipStream_t s);
-// Rows [0, T) of up to three [B, N, H, D] tensors set to zero and, if lse is given, their
-// LSE ([B, H, N]) to -inf.
-hipError_t launch_text_rows(__bf16* x0, __bf16* x1, __bf16* x2, float* lse, int B, int H, int N, int T, int head_dim,
-                            hipStream_t s);
 }  // namespace vcja

@@ -215,12 +215,14 @@ __global__ __launch_bounds__(64 * kWaves, kWavesPerSimd * 4 / kWaves) void fwd_k
     h = ti.h;
     b = ti.b;
   }
+  if (a.frame_len)  // text rows are not queries of the spatial branch
+    write_text_rows<D>(TextRows{a.o, nullptr, nullptr, a.lse, nullptr, nullptr, nullptr}, a.B, a.H, a.N, a.T, tid,
+                       blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z), gridDim.x * gridDim.y * gridDim.z);
   const bool tail = ti.chunk >= 0;
   const int N = a.N;
   const size_t tok = (size_t)a.H * D;
   const size_t base = (size_t)b * N * tok + (size_t)h * D;
-  // This workgroup's queries (spatial branch: inside one frame; text rows are written
-  // by the caller's text-rows pass).
+  // This workgroup's queries (spatial branch: inside one frame).
   const RowBlock rb = row_block(gx, N, a.T, a.frame_len, kBM, false);
   const int qi = rb.r0 + w * 32 + l32;
   const bool q_in = qi < rb.r1;

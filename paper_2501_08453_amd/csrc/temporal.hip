@@ -114,6 +114,8 @@ __global__ __launch_bounds__(64) void temporal_fwd_kernel(TemporalArgs a) {
   VC_LDS char* const k_t = q_t + Tile::REGION;
   VC_LDS char* const v_t = k_t + Tile::REGION;
 
+  write_text_rows<D>(TextRows{a.o, nullptr, nullptr, a.lse, a.sum_a, a.sum_b, SUM ? a.sum_out : nullptr}, a.B, a.H, a.N, a.T,
+                     threadIdx.x, blockIdx.x, gridDim.x);
   const int lane = threadIdx.x & 63;
   const int l32 = lane & 31;
   const int hi = lane >> 5;
@@ -245,6 +247,8 @@ __global__ __launch_bounds__(128) void temporal_bwd_kernel(TemporalArgs a) {
   VC_LDS float* const lse_slot = (VC_LDS float*)(do_t + Tile::REGION);  // LSE*log2(e), +inf if none
   VC_LDS float* const nd_slot = lse_slot + kSlots;                      // -D, 0 if none
 
+  write_text_rows<D>(TextRows{a.o, a.dk, a.dv, nullptr, nullptr, nullptr, nullptr}, a.B, a.H, a.N, a.T, threadIdx.x,
+                     blockIdx.x, gridDim.x);
   const int lane = threadIdx.x & 63;
   const int l32 = lane & 31;
   const int hi = lane >> 5;
@@ -424,29 +428,6 @@ __global__ __launch_bounds__(256) void branch_sum_kernel(const __bf16* a, const 
   *(bf16x4*)(out + off) = bf16x4{(__bf16)acc[0], (__bf16)acc[1], (__bf16)acc[2], (__bf16)acc[3]};
 }
 
-// Zero rows [0, T) of up to three tensors and set their LSE to -inf.
-template <int D>
-__global__ __launch_bounds__(256) void text_rows_kernel(__bf16* x0, __bf16* x1, __bf16* x2, float* lse, int B, int H,
-                                                        int N, int T) {
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;  // one 16-byte chunk
-  constexpr int CPR = D / 8;
-  const size_t rows = (size_t)B * T * H;
-  if (i < rows * CPR) {
-    const size_t row = i / CPR;
-    const int c = (int)(i % CPR);
-    const int hh = (int)(row % H);
-    const size_t bt = row / H;
-    const int t = (int)(bt % T);
-    const int b = (int)(bt / T);
-    const size_t off = (((size_t)b * N + t) * H + hh) * D + c * 8;
-    const bf16x8 z = zero_bf16x8();
-    if (x0) *(bf16x8*)(x0 + off) = z;
-    if (x1) *(bf16x8*)(x1 + off) = z;
-    if (x2) *(bf16x8*)(x2 + off) = z;
-    if (lse && c == 0) lse[((size_t)b * H + hh) * N + t] = -INFINITY;
-  }
-}
-
 }  // namespace
 
 hipError_t launch_temporal_fwd(const TemporalArgs& a, int head_dim, hipStream_t s) {
@@ -480,18 +461,6 @@ hipError_t launch_temporal_bwd(const TemporalArgs& a, int head_dim, hipStream_t 
     hipLaunchKernelGGL(temporal_bwd_kernel<128>, grid, dim3(128), 0, s, a);
   else
     hipLaunchKernelGGL(temporal_bwd_kernel<64>, grid, dim3(128), 0, s, a);
-  return hipGetLastError();
-}
-
-hipError_t launch_text_rows(__bf16* x0, __bf16* x1, __bf16* x2, float* lse, int B, int H, int N, int T, int head_dim,
-                            hipStream_t s) {
-  if (T <= 0) return hipSuccess;
-  const size_t chunks = (size_t)B * T * H * (head_dim / 8);
-  dim3 grid((unsigned)((chunks + 255) / 256));
-  if (head_dim == 128)
-    hipLaunchKernelGGL(text_rows_kernel<128>, grid, dim3(256), 0, s, x0, x1, x2, lse, B, H, N, T);
-  else
-    hipLaunchKernelGGL(text_rows_kernel<64>, grid, dim3(256), 0, s, x0, x1, x2, lse, B, H, N, T);
   return hipGetLastError();
 }
 

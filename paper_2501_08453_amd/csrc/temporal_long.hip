@@ -126,6 +126,8 @@ template <int D, bool SUM>
 __global__ __launch_bounds__(64 * kLongWaves, 1) void temporal_long_fwd_kernel(TemporalArgs a) {
   using Lds = LongLds<D>;
   __shared__ __attribute__((aligned(1024))) char smem[Lds::BYTES];
+  write_text_rows<D>(TextRows{a.o, nullptr, nullptr, a.lse, a.sum_a, a.sum_b, SUM ? a.sum_out : nullptr}, a.B, a.H, a.N, a.T,
+                     threadIdx.x, blockIdx.x, gridDim.x);
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int F = a.F, L = a.L, H = a.H;
   const int nblk = (F + 31) / 32;
@@ -583,6 +585,8 @@ __global__ __launch_bounds__(64 * kLongWaves, 1) void temporal_long_bwd_kernel(T
     }
   }
   wait_all_memory();  // no copy or load of this workgroup outlives it
+  write_text_rows<D>(TextRows{a.o, a.dk, a.dv, nullptr, nullptr, nullptr, nullptr}, a.B, a.H, a.N, a.T,
+                     64 * w + opaque_lane(), blockIdx.x, gridDim.x);
 }
 
 }  // namespace
