@@ -169,7 +169,7 @@ size_t vc_jointattn_bwd_workspace_bytes(const vc_jointattn_desc* desc);
  * different number of compute units the split of the last round of
  * workgroups, and so the summation order of its rows, differs).
  * desc->deterministic = 0: stage 1, vc_jointattn_bwd_fused, then stage 3 over the
- * remaining keys; dk, dv are reproducible run to run, dq only up to the
+ * remaining keys (small problems fuse every key's share of dq here); dk, dv are reproducible run to run, dq only up to the
  * rounding of its fp32 sums. When vc_jointattn_fused_dq_keys(desc) is 0 it
  * runs the deterministic stages instead. */
 vc_status vc_jointattn_bwd(const vc_jointattn_desc* desc,

@@ -192,9 +192,18 @@ int fused_dq_blocks(const vc_jointattn_desc* d, int64_t n) {
   const int pct = d->head_dim == 128 ? kFusedDqPercent128 : kFusedDqPercent64;
   return (int)(((int64_t)nblk * pct + 50) / 100);
 }
-// Every key block carries its dQ share: no dQ pass over key tiles (and no token-major K).
+// Every key block carries its dQ share: no dQ pass over key tiles.
 bool all_keys_fused(const vc_jointattn_desc* d, int64_t n) {
   return (int64_t)fused_dq_blocks(d, n) * vcja::kDkdvKeys >= n;
+}
+
+// Small problems at head_dim 128 form all of dQ in the key-stationary pass too when the whole
+// backward is one call: the dQ pass over 35% of the keys is mostly its launch, prologue and
+// last round there, and the atomics are few. Measured, backward in us at 65% / 100%: 24 heads x
+// 1,280 tokens 134 / 113, 48 x 1,316 216 / 204, 3 x 1,000 57 / 38, 2 x 4,000 98 / 86; beyond,
+// 16 x 2,956 262 / 255, 8 x 4,000 251 / 255, 24 x 2,525 257 / 272, 24 x 5,000 940 / 1048.
+bool fuse_every_key(const vc_jointattn_desc* d, int64_t n) {
+  return dq_offsets_fit(d, n) && (all_keys_fused(d, n) || n <= 2048 || joint_items(d, n) <= 64);
 }
 
 // Forward workspace: V^T tiles | split-tail partials (unnormalised O, base, sum per row).
@@ -464,7 +473,7 @@ vc_status prepare_impl(const vc_jointattn_desc* desc, const void* q, const void*
 vc_status dkdv_impl(const vc_jointattn_desc* desc, const void* q, const void* k, const void* v, const void* dout,
                     const int32_t* text_len, const uint8_t* key_mask, void* dk, void* dv, void* workspace,
                     size_t workspace_bytes, void* stream, bool spatial, bool fused = false,
-                    bool staged = false, bool zero_acc = true) {
+                    bool staged = false, bool zero_acc = true, bool every_key = false) {
   int64_t n = 0;
   vc_status st = check_desc(desc, &n);
   if (st != VC_OK) return st;
@@ -504,7 +513,7 @@ vc_status dkdv_impl(const vc_jointattn_desc* desc, const void* q, const void* k,
   a.dv = static_cast<__bf16*>(dv);
   a.dq_acc = fused ? w.dq_acc : nullptr;
   a.zero_acc = zero_acc;
-  a.dq_blocks = !fused ? 0 : spatial ? std::numeric_limits<int>::max() : fused_dq_blocks(desc, n);
+  a.dq_blocks = !fused ? 0 : spatial || every_key ? std::numeric_limits<int>::max() : fused_dq_blocks(desc, n);
   a.B = desc->batch;
   a.H = desc->heads;
   a.N = (int)n;
@@ -518,7 +527,7 @@ vc_status dkdv_impl(const vc_jointattn_desc* desc, const void* q, const void* k,
 
 vc_status dq_impl(const vc_jointattn_desc* desc, const void* q, const void* k, const void* v, const void* dout,
                   const int32_t* text_len, const uint8_t* key_mask, void* dq, void* workspace,
-                  size_t workspace_bytes, void* stream, bool spatial, bool fused = false) {
+                  size_t workspace_bytes, void* stream, bool spatial, bool fused = false, bool every_key = false) {
   int64_t n = 0;
   vc_status st = check_desc(desc, &n);
   if (st != VC_OK) return st;
@@ -533,7 +542,7 @@ vc_status dq_impl(const vc_jointattn_desc* desc, const void* q, const void* k, c
   // share, plus the accumulator the others filled; when every block added its share, the
   // accumulator alone, scaled and rounded.
   if (fused) {
-    if (spatial || all_keys_fused(desc, n)) {  // spatial: text rows are not queries, their dq is zero
+    if (spatial || every_key || all_keys_fused(desc, n)) {  // spatial: text rows are not queries, their dq is zero
       const size_t tok = (size_t)desc->heads * desc->head_dim;
       return vcja::launch_dq_from_acc(w.dq_acc, static_cast<__bf16*>(dq), desc->batch, n * tok,
                                       spatial ? desc->text_slot * tok : 0, scale_of(desc),
@@ -586,9 +595,10 @@ vc_status bwd_impl(const vc_jointattn_desc* desc, const void* q, const void* k, 
   if (!desc->deterministic && (spatial ? dq_offsets_fit(desc, n) : fused_dq_blocks(desc, n) > 0)) {
     if ((st = prepare_impl(desc, q, k, o, lse, dout, workspace, workspace_bytes, stream, true)) != VC_OK ||
         (st = dkdv_impl(desc, q, k, v, dout, text_len, key_mask, dk, dv, workspace, workspace_bytes, stream,
-                        spatial, true, false, false)) != VC_OK)
+                        spatial, true, false, false, fuse_every_key(desc, n))) != VC_OK)
       return st;
-    return dq_impl(desc, q, k, v, dout, text_len, key_mask, dq, workspace, workspace_bytes, stream, spatial, true);
+    return dq_impl(desc, q, k, v, dout, text_len, key_mask, dq, workspace, workspace_bytes, stream, spatial, true,
+                   fuse_every_key(desc, n));
   }
   if ((st = prepare_impl(desc, q, k, o, lse, dout, workspace, workspace_bytes, stream)) != VC_OK)
     return st;
