@@ -743,8 +743,7 @@ __global__ __launch_bounds__(64 * kDqWaves, 1) void bwd_dq_kernel(DqArgs a) {
   // Completing a fused backward: keys >= kt_min only; joint tail: this chunk's key tiles of them.
   const int kt0 = a.kt_min + (tail ? ti.chunk * a.tail_span : 0);
   if (tail) {
-    runs.a1 = min(runs.a1, kt0 + a.tail_span);
-    runs.b1 = min(runs.b1, kt0 + a.tail_span);
+    runs = runs.clipped(kt0 + a.tail_span);
   }
   auto next_tile = [&](int kt) { return runs.next(kt); };
   // This wave's j-th copies of tile kt's K and V rows into stage st (rows past N repeat row

@@ -286,6 +286,11 @@ struct TileRuns {
   int a1, b0, b1, n;
   // First visited tile >= t, or n when there is none.
   __device__ __forceinline__ int next(int t) const { return t < a1 ? t : (t < b1 ? max(t, b0) : n); }
+  // Those below `end`. A second run that starts at or past it is dropped: next() would else
+  // go on to its first tile (a split workgroup's tiles may all lie in a short caption's padding).
+  __device__ __forceinline__ TileRuns clipped(int end) const {
+    return TileRuns{min(a1, end), b0, b0 < end ? min(b1, end) : 0, n};
+  }
 };
 
 // Workgroups are dispatched round-robin over the XCDs, each with its own L2. With `remap`,

@@ -255,8 +255,7 @@ __global__ __launch_bounds__(64 * kWaves, kWavesPerSimd * 4 / kWaves) void fwd_k
   TileRuns runs = mask.rule.key_tiles(rb.r0, rb.r1, a.ntile);
   const int kt0 = tail ? ti.chunk * a.tail_span : 0;  // joint tail: this chunk's key tiles
   if (tail) {
-    runs.a1 = min(runs.a1, kt0 + a.tail_span);
-    runs.b1 = min(runs.b1, kt0 + a.tail_span);
+    runs = runs.clipped(kt0 + a.tail_span);
   }
   auto next_tile = [&](int kt) { return runs.next(kt); };
   // This wave's j-th copy of tile kt's K or V rows into ring slot `slot` (rows past N repeat

@@ -59,3 +59,32 @@ def test_split_items(shape, least, det):
     assert_close("LSE", lse.cpu().numpy().astype(np.float64), rl)
     for n, a, r in (("O", o, ro), ("dQ", dq, rdq), ("dK", dk, rdk), ("dV", dv, rdv)):
         assert_close(n, bf16_values(a), r)
+
+
+@pytest.mark.parametrize("det", [False, True], ids=["fused", "deterministic"])
+@pytest.mark.parametrize("shape", [(2, 2, 128, 256, 2, 20, 20), (3, 1, 64, 200, 1, 25, 25), (4, 3, 128, 256, 1, 32, 32)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_chunks_inside_caption_padding(shape, det):
+    """Without a key mask the walk skips the tiles of padded text; chunks of a few tiles then lie
+    in a caption's padding in whole or in part and must not go on to another chunk's tiles
+    (a tile counted twice shifts every row of O, LSE and dQ far outside the bounds)."""
+    import torch
+    import paper_2501_08453_amd as vc
+    w = W.custom(*shape)
+    B, N, H, D = w.shape
+    x = W.make_inputs(w, seed=N + D)
+    lens = np.array([5, 70, 130, 0], dtype=np.int32)[:B]
+    g = {n: to_gpu_bf16(x[n]) for n in ("q", "k", "v", "do")}
+    tl = torch.from_numpy(lens).to("cuda")
+    desc = vc.desc_for(w, deterministic=det)
+    o, lse = vc.fwd(g["q"], g["k"], g["v"], desc, tl)
+    dq, dk, dv = vc.bwd(g["q"], g["k"], g["v"], o, lse, g["do"], desc, tl)
+    torch.cuda.synchronize()
+    q, k, v, do = (bf16_values(g[n]) for n in ("q", "k", "v", "do"))
+    valid = ora.key_validity(B, N, w.text_slot, lens)
+    c = ora.default_scale(D)
+    ro, rl = ora.attention_forward(q, k, v, valid, c)
+    rdq, rdk, rdv = ora.attention_backward(q, k, v, do, valid, c, lse=rl)
+    assert_close("LSE", lse.cpu().numpy().astype(np.float64), rl)
+    for n, a, r in (("O", o, ro), ("dQ", dq, rdq), ("dK", dk, rdk), ("dV", dv, rdv)):
+        assert_close(n, bf16_values(a), r)
