@@ -2,7 +2,7 @@
 """Throughput of joint text-video attention (forward + backward) on one MI355X.
 
 One step = one pass of the whole path over one batch of synthetic input:
-forward (O, LSE), backward prepare (D = rowsum(dO o O), token-major copies),
+forward (O, LSE), backward prepare (D = rowsum(dO o O), -LSE / c),
 backward dK/dV and backward dQ, all through the C ABI on torch's current
 stream. Inputs are resident in HBM before timing.
 
@@ -285,8 +285,8 @@ def main(argv=None):
     # Events bracket each stage on the stream the library launches on. Default: the fused
     # backward (stage 1; the key-stationary pass for dK, dV and, for the leading key
     # blocks, their dQ share: the accumulator fill, the kernel, the split tail's sum; the
-    # dQ pass over the other keys); --deterministic: stage 1 with all token-major copies,
-    # the dK/dV pass, the dQ pass over all keys.
+    # dQ pass over the other keys); --deterministic: stage 1, the dK/dV pass, the
+    # dQ pass over all keys.
     def step(ev=None):
         if ev:
             ev[0].record(stream)
