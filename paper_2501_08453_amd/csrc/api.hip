@@ -210,6 +210,20 @@ bool fuse_every_key(const vc_jointattn_desc* d, int64_t n) {
   return dq_offsets_fit(d, n) && (all_keys_fused(d, n) || n <= 2048 || joint_items(d, n) <= 64);
 }
 
+// Spatial backward (deterministic = 0): every key block adds its dQ share with atomics in the
+// key-stationary pass, or the separate passes run. The atomics, one per element and key block of
+// a query's frame at the memory side, set the length of the fused pass; a dQ pass of its own
+// pays for its launch, prologue and last round, so small problems fuse. At head_dim 64 the two
+// are within 3% of each other and all fuse. Measured, D = 128, backward in us, fused / separate
+// (video rows x heads x samples in thousands): 1382 9954 / 9114, 530 2415 / 2100, 196 532 / 453,
+// 173 1320 / 1165, 122 350 / 322, 92 217 / 201 and 723 / 687; 71 212 / 220, 52 76 / 79, 22 260 /
+// 284, 12 162 / 181. D = 64: 1382 5660 / 5522, 307 481 / 487, 262 362 / 373, 74 247 / 252.
+constexpr int64_t kSpatialFusedRows = 80 * 1024;
+bool spatial_fused(const vc_jointattn_desc* d, int64_t n) {
+  return dq_offsets_fit(d, n) &&
+         (d->head_dim == 64 || (n - d->text_slot) * d->heads * d->batch < kSpatialFusedRows);
+}
+
 // Forward workspace: V^T tiles | split-tail partials (unnormalised O, base, sum per row).
 constexpr size_t fwd_wg_bytes(int head_dim) { return (size_t)kRowsPerItem * (head_dim + 2) * sizeof(float); }
 size_t fwd_tail_bytes(const vc_jointattn_desc* d, int64_t n) {
@@ -594,9 +608,9 @@ vc_status bwd_impl(const vc_jointattn_desc* desc, const void* q, const void* k, 
   if (spatial && (st = check_ws(workspace, workspace_bytes, spatial_bwd_ws_bytes(desc, n))) != VC_OK) return st;
   // dQ fused into the key-stationary kernel (atomics) unless the caller asks for bitwise
   // reproducible results: joint attention for its leading key blocks (the dQ pass covers
-  // the others), the spatial branch for every key block (a video query row gets the shares
-  // of 16 key blocks at 720p, so the atomics are few); neither past 32-bit dQ offsets.
-  if (!desc->deterministic && (spatial ? dq_offsets_fit(desc, n) : fused_dq_blocks(desc, n) > 0)) {
+  // the others), the spatial branch, where it fuses, for every key block;
+  // neither past 32-bit dQ offsets.
+  if (!desc->deterministic && (spatial ? spatial_fused(desc, n) : fused_dq_blocks(desc, n) > 0)) {
     if ((st = prepare_impl(desc, q, k, o, lse, dout, workspace, workspace_bytes, stream, true)) != VC_OK ||
         (st = dkdv_impl(desc, q, k, v, dout, text_len, key_mask, dk, dv, workspace, workspace_bytes, stream,
                         spatial, true, false, false, fuse_every_key(desc, n))) != VC_OK)

@@ -153,3 +153,27 @@ def test_spatial_frame_independence_and_joint_reduction():
     b = _run(desc, g2)
     np.testing.assert_array_equal(a["o"][:, :32 + 2 * L], b["o"][:, :32 + 2 * L])
     np.testing.assert_array_equal(a["lse"][:, :, :32 + 2 * L], b["lse"][:, :, :32 + 2 * L])
+
+
+@pytest.mark.parametrize("grid_w", [853, 854, 900])
+def test_backward_routes_agree(grid_w):
+    """Either side of the size from which the default backward runs the separate passes (24
+    heads x 4 frames: 81,920 video rows): dK and dV are bitwise those of the deterministic
+    backward, dQ too from there on, and below up to the order of its fp32 sums, which can move
+    a bf16 result by one rounding: 2^-8 of the value (2-norm)."""
+    import torch
+    import paper_2501_08453_amd as vc
+    B, H, D, T, F = 1, 24, 128, 16, 4
+    N = T + F * grid_w
+    gen = torch.Generator(device="cuda").manual_seed(grid_w)
+    q, k, v, do = (torch.randn((B, N, H, D), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(4))
+    out = []
+    for det in (False, True):
+        desc = vc.make_desc(B, H, D, T, F, 1, grid_w, deterministic=det)
+        o, lse = vc.spatial_fwd(q, k, v, desc)
+        out.append(vc.spatial_bwd(q, k, v, o, lse, do, desc))
+    (dq, dk, dv), (rq, rk, rv) = out
+    assert torch.equal(dk, rk) and torch.equal(dv, rv)
+    if H * F * grid_w >= 80 * 1024:
+        assert torch.equal(dq, rq)
+    assert float((dq.float() - rq.float()).norm() / rq.float().norm()) <= 2.0 ** -8
