@@ -94,10 +94,19 @@ vc_status check_desc(const vc_jointattn_desc* d, int64_t* n_out) {
 float scale_of(const vc_jointattn_desc* d) {
   return d->softmax_scale > 0.0f ? d->softmax_scale : 1.0f / sqrtf((float)d->head_dim);
 }
-// The scale that the joint and spatial backward form probabilities with: c, but no less than
-// 1e-36, so that -LSE / c, where their score accumulators start, stays finite. A score times
-// 1e-36 or less changes no probability either way.
-float prob_scale_of(const vc_jointattn_desc* d) { return std::max(scale_of(d), 1e-36f); }
+// The joint and spatial backward start their score accumulators from -LSE / c, which must stay
+// finite down to the smallest positive c (LSE is about ln N more than the largest c s). Where c
+// is under 1e-30, one factor of the scores is taken times `down` and c divided by it: a
+// power of two, so every probability keeps its value. (bf16 scores reach 1e38, so that even
+// c = 1e-38 gives logits of order 1.)
+struct ProbScale {
+  float c, down;
+};
+ProbScale prob_scale_of(const vc_jointattn_desc* d) {
+  ProbScale p{scale_of(d), 1.0f};
+  for (; p.c < 1e-30f && p.down > 1e-18f; p.c *= 2.0f) p.down *= 0.5f;
+  return p;
+}
 
 int ntiles(int64_t n) { return (int)((n + vcja::kTileTok - 1) / vcja::kTileTok); }
 
@@ -482,7 +491,7 @@ vc_status prepare_impl(const vc_jointattn_desc* desc, const void* q, const void*
   const BwdWorkspace w = split_bwd_ws(desc, n, workspace);
   const int B = desc->batch, H = desc->heads, D = desc->head_dim, N = (int)n;
   hipStream_t s = as_stream(stream);
-  if (vcja::launch_bwd_prepare(bf(o), lse, bf(dout), w.dd, w.nls, B, H, N, ntiles(n) * vcja::kTileTok, D, prob_scale_of(desc),
+  if (vcja::launch_bwd_prepare(bf(o), lse, bf(dout), w.dd, w.nls, B, H, N, ntiles(n) * vcja::kTileTok, D, prob_scale_of(desc).c,
                                zero_acc ? w.dq_acc : nullptr, s) != hipSuccess)
     return VC_ERR_HIP;
   return VC_OK;
@@ -539,7 +548,9 @@ vc_status dkdv_impl(const vc_jointattn_desc* desc, const void* q, const void* k,
   a.ntile = ntiles(n);
   a.frame_len = spatial ? desc->grid_h * desc->grid_w : 0;
   a.scale = scale_of(desc);
-  a.scale_log2 = prob_scale_of(desc) * vcja::kLog2e;
+  const ProbScale ps = prob_scale_of(desc);
+  a.scale_log2 = ps.c * vcja::kLog2e;
+  a.score_down = ps.down;
   return vcja::launch_bwd_dkdv(a, desc->head_dim, as_stream(stream)) == hipSuccess ? VC_OK : VC_ERR_HIP;
 }
 
@@ -594,7 +605,8 @@ vc_status dq_impl(const vc_jointattn_desc* desc, const void* q, const void* k, c
   a.ntile = ntiles(n);
   a.frame_len = spatial ? desc->grid_h * desc->grid_w : 0;
   a.scale = scale_of(desc);
-  a.scale_log2 = prob_scale_of(desc) * vcja::kLog2e;
+  a.scale_log2 = a.scale * vcja::kLog2e;
+  a.nls_log2 = prob_scale_of(desc).c * vcja::kLog2e;
   return vcja::launch_bwd_dq(a, desc->head_dim, as_stream(stream)) == hipSuccess ? VC_OK : VC_ERR_HIP;
 }
 

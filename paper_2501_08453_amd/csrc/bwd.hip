@@ -4,7 +4,8 @@
 //   to whole tiles of 64 rows (padding rows get -inf for the latter so that their
 //   probabilities vanish, and D = 0). So dP - D is what the dP accumulator holds
 //   when it starts from -D, and S - LSE / c (P = exp2 of it times c log2(e)) what
-//   the score accumulator holds when it starts from -LSE / c.
+//   the score accumulator holds when it starts from -LSE / c. (For scales so small that
+//   LSE / c could overflow, a power of two is moved from K to c there.)
 // dK/dV (key-stationary): one workgroup of eight waves owns 256 keys of one
 //   (sample, head), each wave 32, with K and V of its keys in registers and
 //   dK^T, dV^T accumulated in registers. It walks over all query tiles of 32,
@@ -324,6 +325,7 @@ __global__ __launch_bounds__(64 * kDkdvWaves, 1) void bwd_dkdv_kernel(DkdvArgs a
 #pragma unroll
       for (int t = 0; t < 8; ++t) ktl[(16 * ks + 8 * hi + t) * (Lds::KTS / 2) + kl] = kf[ks][t];
   }
+  if (a.score_down != 1.0f) scale_operand(kf, a.score_down);  // the scores' copy of K
 
   f32x16 dk_acc[D / 32], dv_acc[D / 32];
 #pragma unroll
@@ -767,7 +769,7 @@ __global__ __launch_bounds__(64 * kDqWaves, 1) void bwd_dq_kernel(DqArgs a) {
     }
   }
   wait_all_memory();  // the loads above and the first copies: no later wait stands among copies
-  const float nlse2 = nls * a.scale_log2;
+  const float nlse2 = nls * a.nls_log2;
   // Key-mask bytes of each tile loaded a step ahead (waited for at the barrier with the
   // tile's copies), turned into the tile's bits there.
   int kmb = KM && kt < a.ntile ? rule.key_mask_byte(kt, lane) : 1;

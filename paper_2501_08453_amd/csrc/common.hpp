@@ -197,6 +197,16 @@ __device__ __forceinline__ float swap_halves(float x) { return __shfl_xor(x, 32,
 __device__ __forceinline__ float halves_max(float x) { return fmaxf(x, swap_halves(x)); }
 __device__ __forceinline__ float halves_sum(float x) { return x + swap_halves(x); }
 
+// An operand's registers times a power of two (exact but for values that leave bf16's range
+// below).
+template <int K>
+__device__ __forceinline__ void scale_operand(bf16x8 (&x)[K], float f) {
+#pragma unroll
+  for (int k = 0; k < K; ++k)
+#pragma unroll
+    for (int t = 0; t < 8; ++t) x[k][t] = (__bf16)((float)x[k][t] * f);
+}
+
 // Keeps the compiler from moving any instruction across this point.
 __device__ __forceinline__ void sched_fence() { __builtin_amdgcn_sched_barrier(0); }
 
@@ -398,7 +408,7 @@ struct DkdvArgs {
   const __bf16* k;
   const __bf16* v;
   const __bf16* dout;
-  const float* nls;     // -LSE / scale, -inf for rows without keys and padding, [B, H, Npad]
+  const float* nls;     // -LSE * score_down / scale, -inf for rows without keys and padding, [B, H, Npad]
   const float* dd;      // -D = -rowsum(dO o O), 0 on padding, [B, H, Npad]
   const int32_t* text_len;
   const uint8_t* key_mask;
@@ -407,7 +417,8 @@ struct DkdvArgs {
   int B, H, N, T, ntile;
   int frame_len;        // 0: joint attention; > 0: spatial branch
   float scale;          // softmax scale
-  float scale_log2;     // scale * log2(e)
+  float scale_log2;     // scale * log2(e) / score_down
+  float score_down;     // power of two that one factor of the scores is taken times (1 but for tiny scales)
   // Spatial branch, key blocks holding text keys (the first text_blocks): their video query
   // tiles are split into text_chunks runs of text_span tiles, one workgroup each, writing
   // fp32 partial dK, dV (scaled) to text_part, [2][text_chunks][B][H][text_blocks*256][D]
@@ -444,7 +455,8 @@ struct DqArgs {
   int B, H, N, T, ntile;
   int frame_len;        // 0: joint attention; > 0: spatial branch
   float scale;
-  float scale_log2;
+  float scale_log2;     // scale * log2(e)
+  float nls_log2;       // scale * log2(e) / score_down: nls times it is -LSE * log2(e)
   // Joint attention: split tail as for dK/dV, over runs of tail_span key tiles; fp32
   // partial dQ (scaled) in tail_part, [tail_blocks][tail_chunks][256][D].
   float* tail_part;

@@ -60,7 +60,7 @@ def test_infinite_value_in_the_last_row(head_dim):
 def test_tiny_scale(scale, det):
     """The key-stationary pass starts its scores from -LSE / c, which overflows for the smallest
     scales: every probability must still be 1/N (O and dV the oracle's, within the bounds of
-    parity_util; dQ and dK are of the order of the scale)."""
+    parity_util; so dQ and dK over the scale, where bf16 has its full precision)."""
     import paper_2501_08453_amd as vc
     w = W.custom(1, 2, 128, 0, 1, 1, 131)
     x = W.make_inputs(w, seed=5)
@@ -69,7 +69,47 @@ def test_tiny_scale(scale, det):
     q, k, v, do = (bf16_values(g[n]) for n in ("q", "k", "v", "do"))
     valid = np.ones((1, 131), dtype=bool)
     o, lse = ora.attention_forward(q, k, v, valid, scale)
-    _, _, dv = ora.attention_backward(q, k, v, do, valid, scale, lse=lse)
+    dq, dk, dv = ora.attention_backward(q, k, v, do, valid, scale, lse=lse)
     assert_close("O", out["o"], o)
     assert_close("dV", out["dv"], dv)
+    if scale == 1e-30:
+        assert_close("dQ/c", out["dq"] / scale, dq / scale)
+        assert_close("dK/c", out["dk"] / scale, dk / scale)
     assert np.abs(out["dq"]).max() < 1e3 * scale and np.abs(out["dk"]).max() < 1e3 * scale
+
+
+@pytest.mark.parametrize("det", [False, True], ids=["fused", "deterministic"])
+@pytest.mark.parametrize("branch", ["joint", "spatial"])
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("scale", [1e-20, 1e-30, 1e-37, 1e-39, 1e20, 1e37])
+def test_extreme_scales_with_matching_scores(scale, head_dim, branch, det):
+    """Extreme scales are used with scores of the inverse size: q and k such that the logits c q.k are of
+    order 0.5 (scores up to about 2e38 of the 3.4e38 that fp32 holds; for 1e-39 a tenth of
+    that). Results are those of ordinary sizes: dQ and dK are compared in units of c |k|
+    and c |q|, within the bounds of parity_util."""
+    import torch
+    import oracle.ref_branches as orb
+    import paper_2501_08453_amd as vc
+    T, F = (16, 2) if branch == "spatial" else (0, 1)
+    w = W.custom(1, 2, head_dim, T, F, 1, 99)
+    x = W.make_inputs(w, seed=7)
+    size = np.sqrt(min(0.5 / scale, 5e37) / np.sqrt(head_dim))  # of a q or k element
+    g = {n: to_gpu_bf16(x[n] * (np.float32(size) if n in "qk" else np.float32(1))) for n in ("q", "k", "v", "do")}
+    q, k, v, do = (bf16_values(g[n]) for n in ("q", "k", "v", "do"))
+    desc = vc.desc_for(w, scale=scale, deterministic=det)
+    if branch == "joint":
+        out = run_gpu(desc, g["q"], g["k"], g["v"], g["do"])
+        valid = np.ones((1, w.tokens), dtype=bool)
+        o, lse = ora.attention_forward(q, k, v, valid, scale)
+        dq, dk, dv = ora.attention_backward(q, k, v, do, valid, scale, lse=lse)
+    else:
+        to, tl = vc.spatial_fwd(g["q"], g["k"], g["v"], desc)
+        grads = vc.spatial_bwd(g["q"], g["k"], g["v"], to, tl, g["do"], desc)
+        torch.cuda.synchronize()
+        out = dict(zip(("o", "dq", "dk", "dv"), map(bf16_values, (to, *grads))))
+        o, lse = orb.spatial_forward(q, k, v, T, F, scale=scale)
+        dq, dk, dv = orb.spatial_backward(q, k, v, do, T, F, scale=scale, lse=lse)
+    unit = scale * size
+    for n, a, r in (("O", out["o"], o), ("dV", out["dv"], dv), ("dQ", out["dq"] / unit, dq / unit),
+                    ("dK", out["dk"] / unit, dk / unit)):
+        assert_close(n, a, r)
