@@ -268,9 +268,9 @@ vc_status vc_spatialattn_fwd(const vc_jointattn_desc* desc,
  * adds every key block's share of dq to an fp32 accumulator with atomics (a video
  * query row gets the shares of its frame's key blocks and of the text block); dk,
  * dv are reproducible run to run, dq only up to the rounding of its fp32 sums.
- * Where they are the faster way (at head_dim 128, from 81,920 video rows over all heads and samples on),
- * and when a sample's N*H*D elements reach 2^32, the separate passes run for
- * either value of the flag. */
+ * Where they are the faster way (at head_dim 128, without a key mask, frames of more than 160
+ * tokens, from 81,920 video rows over all heads and samples on), and when a sample's N*H*D
+ * elements reach 2^32, the separate passes run for either value of the flag. */
 vc_status vc_spatialattn_bwd(const vc_jointattn_desc* desc,
                              const void* q, const void* k, const void* v,
                              const void* o, const float* lse, const void* dout,

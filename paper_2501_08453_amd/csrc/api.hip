@@ -222,15 +222,23 @@ bool fuse_every_key(const vc_jointattn_desc* d, int64_t n) {
 // Spatial backward (deterministic = 0): every key block adds its dQ share with atomics in the
 // key-stationary pass, or the separate passes run. The atomics, one per element and key block of
 // a query's frame at the memory side, set the length of the fused pass; a dQ pass of its own
-// pays for its launch, prologue and last round, so small problems fuse. At head_dim 64 the two
-// are within 3% of each other and all fuse. Measured, D = 128, backward in us, fused / separate
-// (video rows x heads x samples in thousands): 1382 9954 / 9114, 530 2415 / 2100, 196 532 / 453,
-// 173 1320 / 1165, 122 350 / 322, 92 217 / 201 and 723 / 687; 71 212 / 220, 52 76 / 79, 22 260 /
-// 284, 12 162 / 181. D = 64: 1382 5660 / 5522, 307 481 / 487, 262 362 / 373, 74 247 / 252.
+// pays for its launch, prologue and last round, so small problems fuse, and so do frames of
+// up to 160 tokens, which leave much of a dQ workgroup's 256 rows empty. With a key mask the dQ
+// pass tests every key of every tile against the mask and its frame's bounds, and loses. At
+// head_dim 64 the two are within 3% of each other and all fuse. Measured, D = 128, backward in
+// us, fused / separate (video rows x heads x samples in thousands): 1382 9889 / 8406, 530 2415 /
+// 2100, 322 2218 / 1940, 196 532 / 453 and 308 / 274, 173 1320 / 1165, 122 350 / 322, 92 217 / 201
+// and 751 / 671; 71 212 / 220, 52 76 / 79, 22 260 / 284, 12 162 / 181. Frames of 48 tokens 319 /
+// 423 and 210 / 244, of 100 519 / 549 and 285 / 311, of 120 321 / 363, of 128 175 / 172 and 419 /
+// 433, of 144 192 / 190 and 372 / 404, of 192 463 / 447, of 240 212 / 200. Masked: 1382 9919 /
+// 11019, 794 3696 / 4184, 614 1820 / 2051, 122 266 / 278, 92 (frames of 60) 192 / 235. D = 64: 1382
+// 5660 / 5522, 307 481 / 487, 262 362 / 373, 74 247 / 252.
 constexpr int64_t kSpatialFusedRows = 80 * 1024;
-bool spatial_fused(const vc_jointattn_desc* d, int64_t n) {
+constexpr int kSpatialFusedFrame = 160;
+bool spatial_fused(const vc_jointattn_desc* d, int64_t n, bool key_mask) {
   return dq_offsets_fit(d, n) &&
-         (d->head_dim == 64 || (n - d->text_slot) * d->heads * d->batch < kSpatialFusedRows);
+         (d->head_dim == 64 || key_mask || (int64_t)d->grid_h * d->grid_w <= kSpatialFusedFrame ||
+          (n - d->text_slot) * d->heads * d->batch < kSpatialFusedRows);
 }
 
 // Forward workspace: V^T tiles | split-tail partials (unnormalised O, base, sum per row).
@@ -622,7 +630,7 @@ vc_status bwd_impl(const vc_jointattn_desc* desc, const void* q, const void* k, 
   // reproducible results: joint attention for its leading key blocks (the dQ pass covers
   // the others), the spatial branch, where it fuses, for every key block;
   // neither past 32-bit dQ offsets.
-  if (!desc->deterministic && (spatial ? spatial_fused(desc, n) : fused_dq_blocks(desc, n) > 0)) {
+  if (!desc->deterministic && (spatial ? spatial_fused(desc, n, key_mask != nullptr) : fused_dq_blocks(desc, n) > 0)) {
     if ((st = prepare_impl(desc, q, k, o, lse, dout, workspace, workspace_bytes, stream, true)) != VC_OK ||
         (st = dkdv_impl(desc, q, k, v, dout, text_len, key_mask, dk, dv, workspace, workspace_bytes, stream,
                         spatial, true, false, false, fuse_every_key(desc, n))) != VC_OK)

@@ -177,3 +177,26 @@ def test_backward_routes_agree(grid_w):
     if H * F * grid_w >= 80 * 1024:
         assert torch.equal(dq, rq)
     assert float((dq.float() - rq.float()).norm() / rq.float().norm()) <= 2.0 ** -8
+
+
+@pytest.mark.parametrize("grid_w,masked,separate", [(854, False, True), (853, False, False), (900, True, False),
+                                                    (161, False, True), (160, False, False)])
+def test_backward_route(grid_w, masked, separate):
+    """Which of the two ways the default backward takes at head_dim 128: the separate passes from
+    81,920 video rows on, but never with a key mask or frames of 160 tokens or fewer, where
+    they are slower. The fused way is known by its dQ accumulator, which it fills in the
+    workspace after the two per-row arrays; the separate passes leave that place alone."""
+    import torch
+    import paper_2501_08453_amd as vc
+    B, H, D, T, F = 1, 24, 128, 16, 4 if grid_w > 500 else 32
+    N = T + F * grid_w
+    gen = torch.Generator(device="cuda").manual_seed(grid_w)
+    q, k, v, do = (torch.randn((B, N, H, D), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(4))
+    km = (torch.rand((B, N), generator=gen, device="cuda") < 0.9).to(torch.uint8) if masked else None
+    desc = vc.make_desc(B, H, D, T, F, 1, grid_w)
+    o, lse = vc.spatial_fwd(q, k, v, desc, None, km)
+    ws = vc.spatial_workspace(desc, "cuda").fill_(0xA5)
+    vc.spatial_bwd(q, k, v, o, lse, do, desc, None, km, ws=ws)
+    acc = 2 * B * H * ((N + 63) // 64 * 64) * 4  # a multiple of 256
+    touched = bool((ws[acc:acc + B * N * H * D * 4] != 0xA5).any())
+    assert touched != separate
