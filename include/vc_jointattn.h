@@ -169,8 +169,10 @@ size_t vc_jointattn_bwd_workspace_bytes(const vc_jointattn_desc* desc);
  * different number of compute units the split of the last round of
  * workgroups, and so the summation order of its rows, differs).
  * desc->deterministic = 0: stage 1, vc_jointattn_bwd_fused, then stage 3 over the
- * remaining keys (small problems fuse every key's share of dq here); dk, dv are reproducible run to run, dq only up to the
- * rounding of its fp32 sums. When vc_jointattn_fused_dq_keys(desc) is 0 it
+ * remaining keys (at head_dim 128, small problems fuse every key's share of dq here: N up to
+ * 1,024; up to 2,048 with at most 448 blocks of 256 rows over all heads and samples; up to
+ * 14,336 with at most 64); dk, dv are reproducible run to run, dq only up to the rounding of
+ * its fp32 sums. When vc_jointattn_fused_dq_keys(desc) is 0 it
  * runs the deterministic stages instead. */
 vc_status vc_jointattn_bwd(const vc_jointattn_desc* desc,
                            const void* q, const void* k, const void* v,

@@ -187,10 +187,11 @@ size_t tail_part_bytes(const vc_jointattn_desc* d, int64_t n) {
 // the key-stationary pass; the dQ pass covers the others. Per key block, the atomics (an
 // fp32 dQ tile per query tile) cost about what the dQ pass's recomputation of S and dP
 // costs at head_dim 128, so the backward's time is nearly flat in the fraction between 1/2
-// and 7/8 there; 65% measured fastest on the long workload (ragged-text and max-length
-// workloads: within 1% from 65% to 80%). At head_dim 64 fusing every key block is fastest
-// (medium workload: 1.85 ms against 2.02 at 65% and 2.11 for the separate passes); the dQ
-// pass then only converts the accumulator.
+// and 7/8 there. Measured, us at 0, 50, 65, 80, 100%: 24 heads x 20,000 tokens 13558, 13706, 13293,
+// 13812, 15629; 64 x 9,856 9001, 9224, 9018, 8942, 9879; 24 x 5,000 914, 947, 921, 945, 1040. At
+// head_dim 64 fusing every key block is fastest on clips of some thousand tokens (32 x 8,320 1938,
+// 1989, 1920, 1885, 1802; 48 x 4,000 692, 736, 707, 681, 663) and within 5% of the best beyond
+// (24 x 20,000 8144, 8471, 8380, 8023, 8401); the dQ pass then only converts the accumulator.
 constexpr int kFusedDqPercent128 = 65;
 constexpr int kFusedDqPercent64 = 100;
 // The fused pass addresses a sample's fp32 dQ accumulator with 32-bit element offsets, so it
@@ -212,11 +213,18 @@ bool all_keys_fused(const vc_jointattn_desc* d, int64_t n) {
 
 // Small problems at head_dim 128 form all of dQ in the key-stationary pass too when the whole
 // backward is one call: the dQ pass over 35% of the keys is mostly its launch, prologue and
-// last round there, and the atomics are few. Measured, backward in us at 65% / 100%: 24 heads x
-// 1,280 tokens 134 / 113, 48 x 1,316 216 / 204, 3 x 1,000 57 / 38, 2 x 4,000 98 / 86; beyond,
-// 16 x 2,956 262 / 255, 8 x 4,000 251 / 255, 24 x 2,525 257 / 272, 24 x 5,000 940 / 1048.
+// last round there, and the atomics are few. From a few rounds of workgroups on, that pass is
+// cheap and the atomics of long samples are not. Measured, backward in us at 65% / 100%, (heads x
+// samples) x tokens: 384 x 512 294 / 266, 768 x 512 620 / 526, 384 x 768 574 / 530, 192 x 1,024
+// 416 / 418, 1536 x 1,024 3350 / 3128; 24 x 1,280 134 / 113, 72 x 1,280 290 / 263, 48 x 1,792
+// 318 / 307, 24 x 2,048 199 / 189, 48 x 2,048 396 / 385 and 381 / 386, 72 x 1,536 345 / 327; 3 x
+// 1,000 57 / 38, 4 x 4,000 149 / 141, 1 x 12,000 273 / 265, 1 x 14,000 363 / 344. Not so: 96 x
+// 1,280 304 / 314, 192 x 1,280 611 / 616, 96 x 2,048 687 / 722, 1 x 16,384 444 / 460, 16 x 4,096
+// 401 / 448, 24 x 2,525 257 / 272, 24 x 5,000 921 / 1040.
 bool fuse_every_key(const vc_jointattn_desc* d, int64_t n) {
-  return dq_offsets_fit(d, n) && (all_keys_fused(d, n) || n <= 2048 || joint_items(d, n) <= 64);
+  const int64_t items = joint_items(d, n);
+  return dq_offsets_fit(d, n) && (all_keys_fused(d, n) || n <= 1024 || (n <= 2048 && items <= 448) ||
+                                  (n <= 14336 && items <= 64));
 }
 
 // Spatial backward (deterministic = 0): every key block adds its dQ share with atomics in the

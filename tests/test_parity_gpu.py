@@ -390,3 +390,24 @@ def test_staged_backward_calls(head_dim):
             assert torch.equal(dq, ref[0])
         else:
             assert _same_up_to_order(bf16_values(dq), bf16_values(ref[0]), "dQ staged vs one call")
+
+
+@pytest.mark.parametrize("heads,tokens,every_key", [(120, 1024, True), (96, 1025, False), (56, 2048, True),
+                                                    (57, 2048, False), (1, 14336, True), (1, 14337, False),
+                                                    (9, 2049, False)])
+def test_one_call_backward_fuses_every_key_of_small_problems(heads, tokens, every_key):
+    """Where the default one-call backward at head_dim 128 forms all of dQ in the key-stationary
+    pass: dq is then the scaled and rounded fp32 accumulator (in the workspace after the two
+    per-row arrays), bit for bit; elsewhere the accumulator lacks the keys of the dQ pass."""
+    import torch
+    import paper_2501_08453_amd as vc
+    gen = torch.Generator(device="cuda").manual_seed(tokens)
+    shape = (1, tokens, heads, 128)
+    q, k, v, do = (torch.randn(shape, generator=gen, device="cuda").to(torch.bfloat16) for _ in range(4))
+    desc = vc.make_desc(1, heads, 128, 0, 1, 1, tokens, scale=0.125)
+    o, lse = vc.fwd(q, k, v, desc)
+    ws = vc.workspace(desc, "cuda")
+    dq, _, _ = vc.bwd(q, k, v, o, lse, do, desc, ws=ws)
+    at = 2 * ((heads * ((tokens + 63) // 64 * 64) * 4 + 255) // 256 * 256)
+    acc = ws[at:at + q.numel() * 4].view(torch.float32).view(shape)
+    assert torch.equal(dq, (acc * 0.125).to(torch.bfloat16)) == every_key
