@@ -426,7 +426,7 @@ vc_status fwd_impl(const vc_jointattn_desc* desc, const void* q, const void* k, 
     return VC_ERR_ALIGN;
   if ((st = check_ws(workspace, workspace_bytes, fwd_ws_bytes(desc, n))) != VC_OK) return st;
   if ((st = check_device()) != VC_OK) return st;
-  vcja::FwdArgs a;
+  vcja::FwdArgs a{};
   a.q = bf(q);
   a.k = bf(k);
   a.v = bf(v);

@@ -211,10 +211,12 @@ __device__ __forceinline__ void scale_operand(bf16x8 (&x)[K], float f) {
 __device__ __forceinline__ void sched_fence() { __builtin_amdgcn_sched_barrier(0); }
 
 // Rows [0, T) of up to three [B, N, H, D] tensors set to zero and, if lse is given, their LSE
-// ([B, H, N]) to -inf: the text rows of the branches in which text is no query, written by
-// the first threads of the branch's own grid. (A launch of their own took 5 us, a quarter of
-// a small temporal forward: 20.2 -> 17.1 us a call.) Every workgroup calls it. With `sum`, rows of sum = (sum_a + sum_b) too (fp32, rounded once; a
-// NULL input counts as zero).
+// ([B, H, N]) to -inf: the text rows of the branches in which text is no query. With `sum`,
+// rows of sum = (sum_a + sum_b) too (fp32, rounded once; a NULL input counts as zero). Written by
+// the first threads of the branch's own grid (every workgroup calls write_text_rows), as a launch
+// of their own takes 3 to 5 us, a quarter of a small temporal forward (10.3 -> 7.6 us a call),
+// or, where a long text meets a small video and each thread of that grid would write many 16-byte
+// chunks, by that launch after all (place_text_rows).
 struct TextRows {
   __bf16 *x0, *x1, *x2;
   float* lse;
@@ -392,6 +394,9 @@ struct FwdArgs {
   const uint8_t* key_mask;
   __bf16* o;
   float* lse;
+  // A spatial kernel reads B only as the number of samples whose text rows it writes: the
+  // launcher passes 0 where they have a launch of their own (a further argument, or any test
+  // of it, made the joint instances 1 to 2% slower by other scalar spills in their loop).
   int B, H, N, T, ntile;  // ntile = tiles of 64 tokens per (sample, head)
   int frame_len;          // 0: joint attention; > 0: spatial branch with frames of this many tokens
   float scale_log2;       // softmax scale times log2(e)
@@ -452,7 +457,7 @@ struct DqArgs {
   const int32_t* text_len;
   const uint8_t* key_mask;
   __bf16* dq;
-  int B, H, N, T, ntile;
+  int B, H, N, T, ntile;  // B as in FwdArgs
   int frame_len;        // 0: joint attention; > 0: spatial branch
   float scale;
   float scale_log2;     // scale * log2(e)
@@ -493,6 +498,7 @@ struct TemporalArgs {
   int B, H, N, T, F, L, G, npad;
   float scale;
   float scale_log2;
+  int text_rows;        // text rows the kernel writes, T or 0 (set by the launcher)
 };
 
 }  // namespace vcja
@@ -504,10 +510,14 @@ hipError_t launch_bwd_prepare(const __bf16* o, const float* lse, const __bf16* d
                               int H, int N, int Npad, int head_dim, float scale, float* zero_acc, hipStream_t s);
 hipError_t launch_bwd_dkdv(const DkdvArgs& a, int head_dim, hipStream_t s);
 hipError_t launch_bwd_dq(const DqArgs& a, int head_dim, hipStream_t s);
+// Launches the text rows of a branch on their own where its grid of `threads` had better not
+// write them; *in_grid: those that are left to it, T or 0.
+hipError_t place_text_rows(const TextRows& t, int B, int H, int N, int T, int head_dim, size_t threads, hipStream_t s,
+                           int* in_grid);
+hipError_t launch_zero_f32(float* x, size_t n, hipStream_t s);  // n a multiple of 4
 // dq = bf16(scale * acc) over n elements (a fused backward whose key blocks all added their
 // dQ share to the fp32 accumulator acc, [B, N, H, D] like dq). n a multiple of 4.
 // The first `zero` of each sample's elements are written as zero instead.
-hipError_t launch_zero_f32(float* x, size_t n, hipStream_t s);  // n a multiple of 4
 hipError_t launch_dq_from_acc(const float* acc, __bf16* dq, int B, size_t per_sample, size_t zero, float scale,
                               hipStream_t s);
 hipError_t launch_temporal_fwd(const TemporalArgs& a, int head_dim, hipStream_t s);

@@ -479,10 +479,18 @@ __global__ void tail_merge_kernel(const float* part, __bf16* o, float* lse, int 
 
 }  // namespace
 
-hipError_t launch_fwd(const FwdArgs& a, int head_dim, hipStream_t s) {
+hipError_t launch_fwd(const FwdArgs& args, int head_dim, hipStream_t s) {
+  FwdArgs a = args;
   const int nblk = row_blocks(a.N, a.T, a.frame_len, kBM, false);
+  int text_rows = a.T;  // of them in the spatial kernel's grid
+  if (a.frame_len) {
+    const hipError_t e = place_text_rows(TextRows{a.o, nullptr, nullptr, a.lse, nullptr, nullptr, nullptr}, a.B, a.H, a.N, a.T,
+                                         head_dim, (size_t)nblk * a.H * a.B * 64 * kWaves, s, &text_rows);
+    if (e != hipSuccess) return e;
+  }
   // Spatial: 3-D grid renumbered by XCD. Joint: 1-D grid of items, the split tail last.
   dim3 grid = a.frame_len ? dim3(nblk, a.H, a.B) : dim3(nblk * a.H * a.B + a.tail_blocks * (a.tail_chunks - 1));
+  if (a.frame_len && !text_rows) a.B = 0;
   const bool km = a.key_mask != nullptr;
   if (head_dim == 128 && km)
     hipLaunchKernelGGL((fwd_kernel<128, true>), grid, dim3(64 * kWaves), 0, s, a);

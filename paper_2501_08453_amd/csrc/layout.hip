@@ -1,4 +1,7 @@
-// The backward's fp32 dQ accumulator: clearing it, and turning it into dQ. Memory-bound.
+// Memory-bound passes: the backward's fp32 dQ accumulator cleared and turned into dQ, and the
+// text rows of the branches where the branch's own grid does not write them.
+#include <algorithm>
+
 #include "common.hpp"
 
 namespace vcja {
@@ -20,7 +23,31 @@ __global__ void zero_f32_kernel(float* x, size_t n4) {
   if (i < n4) ((f32x4*)x)[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 }
 
+template <int D>
+__global__ __launch_bounds__(256) void text_rows_kernel(TextRows t, int B, int H, int N, int T) {
+  write_text_rows<D>(t, B, H, N, T, threadIdx.x, blockIdx.x, gridDim.x);
+}
+
 }  // namespace
+
+// In the branch's grid up to 16 chunks a thread, up to 8 with a sum, whose reads a thread waits
+// for. Measured, us a call, in the grid / apart: temporal forward at 3.6 chunks 7.6 / 10.3, 11
+// 9.7 / 10.0, 21 11.8 / 10.1, 64 25.8 / 9.9; with the sum 9.4 / 13.3, 17.3 / 16.7, 17.1 / 13.4,
+// 38.2 / 13.3; backward at 11 9.8 / 10.7, 32 12.3 / 10.8; spatial forward at 16 49.5 / 50.8, 128
+// 159 / 117.
+hipError_t place_text_rows(const TextRows& t, int B, int H, int N, int T, int head_dim, size_t threads, hipStream_t s,
+                           int* in_grid) {
+  const size_t chunks = (size_t)B * T * H * (head_dim / 8);
+  const bool apart = chunks > (t.sum ? 8 : 16) * threads;
+  *in_grid = apart ? 0 : T;
+  if (!apart) return hipSuccess;
+  const dim3 grid((unsigned)std::min<size_t>((chunks + 255) / 256, 1 << 20));
+  if (head_dim == 128)
+    hipLaunchKernelGGL(text_rows_kernel<128>, grid, dim3(256), 0, s, t, B, H, N, T);
+  else
+    hipLaunchKernelGGL(text_rows_kernel<64>, grid, dim3(256), 0, s, t, B, H, N, T);
+  return hipGetLastError();
+}
 
 hipError_t launch_zero_f32(float* x, size_t n, hipStream_t s) {
   const size_t n4 = n / 4;

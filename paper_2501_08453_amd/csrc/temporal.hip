@@ -114,8 +114,8 @@ __global__ __launch_bounds__(64) void temporal_fwd_kernel(TemporalArgs a) {
   VC_LDS char* const k_t = q_t + Tile::REGION;
   VC_LDS char* const v_t = k_t + Tile::REGION;
 
-  write_text_rows<D>(TextRows{a.o, nullptr, nullptr, a.lse, a.sum_a, a.sum_b, SUM ? a.sum_out : nullptr}, a.B, a.H, a.N, a.T,
-                     threadIdx.x, blockIdx.x, gridDim.x);
+  write_text_rows<D>(TextRows{a.o, nullptr, nullptr, a.lse, a.sum_a, a.sum_b, SUM ? a.sum_out : nullptr}, a.B, a.H, a.N,
+                     a.text_rows, threadIdx.x, blockIdx.x, gridDim.x);
   const int lane = threadIdx.x & 63;
   const int l32 = lane & 31;
   const int hi = lane >> 5;
@@ -247,8 +247,8 @@ __global__ __launch_bounds__(128) void temporal_bwd_kernel(TemporalArgs a) {
   VC_LDS float* const lse_slot = (VC_LDS float*)(do_t + Tile::REGION);  // LSE*log2(e), +inf if none
   VC_LDS float* const nd_slot = lse_slot + kSlots;                      // -D, 0 if none
 
-  write_text_rows<D>(TextRows{a.o, a.dk, a.dv, nullptr, nullptr, nullptr, nullptr}, a.B, a.H, a.N, a.T, threadIdx.x,
-                     blockIdx.x, gridDim.x);
+  write_text_rows<D>(TextRows{a.o, a.dk, a.dv, nullptr, nullptr, nullptr, nullptr}, a.B, a.H, a.N, a.text_rows,
+                     threadIdx.x, blockIdx.x, gridDim.x);
   const int lane = threadIdx.x & 63;
   const int l32 = lane & 31;
   const int hi = lane >> 5;
@@ -430,9 +430,13 @@ __global__ __launch_bounds__(256) void branch_sum_kernel(const __bf16* a, const 
 
 }  // namespace
 
-hipError_t launch_temporal_fwd(const TemporalArgs& a, int head_dim, hipStream_t s) {
+hipError_t launch_temporal_fwd(const TemporalArgs& args, int head_dim, hipStream_t s) {
+  TemporalArgs a = args;
   const int nblk = (a.L + a.G - 1) / a.G;
   const dim3 grid((unsigned)((size_t)a.B * nblk * a.H));
+  const hipError_t e = place_text_rows(TextRows{a.o, nullptr, nullptr, a.lse, a.sum_a, a.sum_b, a.sum_out}, a.B, a.H, a.N, a.T,
+                                       head_dim, (size_t)grid.x * 64, s, &a.text_rows);
+  if (e != hipSuccess) return e;
   const bool sum = a.sum_out != nullptr;
   if (head_dim == 128 && sum)
     hipLaunchKernelGGL((temporal_fwd_kernel<128, true>), grid, dim3(64), 0, s, a);
@@ -454,9 +458,13 @@ hipError_t launch_branch_sum(const __bf16* a, const __bf16* b, const __bf16* c, 
   return hipGetLastError();
 }
 
-hipError_t launch_temporal_bwd(const TemporalArgs& a, int head_dim, hipStream_t s) {
+hipError_t launch_temporal_bwd(const TemporalArgs& args, int head_dim, hipStream_t s) {
+  TemporalArgs a = args;
   const int nblk = (a.L + a.G - 1) / a.G;
   const dim3 grid((unsigned)((size_t)a.B * nblk * a.H));
+  const hipError_t e = place_text_rows(TextRows{a.o, a.dk, a.dv, nullptr, nullptr, nullptr, nullptr}, a.B, a.H, a.N, a.T,
+                                       head_dim, (size_t)grid.x * 128, s, &a.text_rows);
+  if (e != hipSuccess) return e;
   if (head_dim == 128)
     hipLaunchKernelGGL(temporal_bwd_kernel<128>, grid, dim3(128), 0, s, a);
   else

@@ -126,8 +126,8 @@ template <int D, bool SUM>
 __global__ __launch_bounds__(64 * kLongWaves, 1) void temporal_long_fwd_kernel(TemporalArgs a) {
   using Lds = LongLds<D>;
   __shared__ __attribute__((aligned(1024))) char smem[Lds::BYTES];
-  write_text_rows<D>(TextRows{a.o, nullptr, nullptr, a.lse, a.sum_a, a.sum_b, SUM ? a.sum_out : nullptr}, a.B, a.H, a.N, a.T,
-                     threadIdx.x, blockIdx.x, gridDim.x);
+  write_text_rows<D>(TextRows{a.o, nullptr, nullptr, a.lse, a.sum_a, a.sum_b, SUM ? a.sum_out : nullptr}, a.B, a.H, a.N,
+                     a.text_rows, threadIdx.x, blockIdx.x, gridDim.x);
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int F = a.F, L = a.L, H = a.H;
   const int nblk = (F + 31) / 32;
@@ -585,15 +585,19 @@ __global__ __launch_bounds__(64 * kLongWaves, 1) void temporal_long_bwd_kernel(T
     }
   }
   wait_all_memory();  // no copy or load of this workgroup outlives it
-  write_text_rows<D>(TextRows{a.o, a.dk, a.dv, nullptr, nullptr, nullptr, nullptr}, a.B, a.H, a.N, a.T,
+  write_text_rows<D>(TextRows{a.o, a.dk, a.dv, nullptr, nullptr, nullptr, nullptr}, a.B, a.H, a.N, a.text_rows,
                      64 * w + opaque_lane(), blockIdx.x, gridDim.x);
 }
 
 }  // namespace
 
-hipError_t launch_temporal_long_fwd(const TemporalArgs& a, int head_dim, int cus, hipStream_t s) {
+hipError_t launch_temporal_long_fwd(const TemporalArgs& args, int head_dim, int cus, hipStream_t s) {
+  TemporalArgs a = args;
   const int items = a.B * a.L * a.H;
   dim3 grid((unsigned)std::max(1, std::min(items, cus)));
+  const hipError_t e = place_text_rows(TextRows{a.o, nullptr, nullptr, a.lse, a.sum_a, a.sum_b, a.sum_out}, a.B, a.H, a.N, a.T,
+                                       head_dim, (size_t)grid.x * 64 * kLongWaves, s, &a.text_rows);
+  if (e != hipSuccess) return e;
   const bool sum = a.sum_out != nullptr;
   if (head_dim == 128 && sum)
     hipLaunchKernelGGL((temporal_long_fwd_kernel<128, true>), grid, dim3(64 * kLongWaves), 0, s, a);
@@ -606,9 +610,13 @@ hipError_t launch_temporal_long_fwd(const TemporalArgs& a, int head_dim, int cus
   return hipGetLastError();
 }
 
-hipError_t launch_temporal_long_bwd(const TemporalArgs& a, int head_dim, int cus, hipStream_t s) {
+hipError_t launch_temporal_long_bwd(const TemporalArgs& args, int head_dim, int cus, hipStream_t s) {
+  TemporalArgs a = args;
   const int items = a.B * a.L * a.H;
   dim3 grid((unsigned)std::max(1, std::min(items, cus)));
+  const hipError_t e = place_text_rows(TextRows{a.o, a.dk, a.dv, nullptr, nullptr, nullptr, nullptr}, a.B, a.H, a.N, a.T,
+                                       head_dim, (size_t)grid.x * 64 * kLongWaves, s, &a.text_rows);
+  if (e != hipSuccess) return e;
   if (head_dim == 128)
     hipLaunchKernelGGL(temporal_long_bwd_kernel<128>, grid, dim3(64 * kLongWaves), 0, s, a);
   else

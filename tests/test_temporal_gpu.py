@@ -221,3 +221,37 @@ def test_temporal_deterministic_and_text_independent():
     for n in a:
         np.testing.assert_array_equal(a[n], c[n])
     del torch
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("text", [3, 127, 128, 129, 700])
+@pytest.mark.parametrize("frames", [2, 16, 40])
+def test_text_rows_of_little_video(frames, text, head_dim):
+    """The text rows of the branches, written by the branch's own grid or, from some chunks of 16
+    bytes a thread on, by a launch of their own (here: one position, so few threads): zero in
+    O, dQ, dK and dV of the temporal branch and in O and dQ of the spatial one, LSE -inf, the
+    fused sum bitwise that of vc_branchsum; the video rows are finite."""
+    import torch
+    import paper_2501_08453_amd as vc
+    B, H, N = 2, 3, text + frames
+    gen = torch.Generator(device="cuda").manual_seed(text)
+    q, k, v, do, oj, os_ = (torch.randn((B, N, H, head_dim), generator=gen, device="cuda").to(torch.bfloat16)
+                            for _ in range(6))
+    desc = vc.make_desc(B, H, head_dim, text, frames, 1, 1, deterministic=True)
+    nan = lambda: torch.full_like(q, float("nan"))  # noqa: E731
+    nan_lse = lambda: torch.full((B, H, N), float("nan"), device="cuda")  # noqa: E731
+    o, lse, out = nan(), nan_lse(), nan()
+    vc.vc_temporalattn_fwd_sum(desc, q, k, v, None, oj, os_, o, lse, out)
+    o1, lse1 = vc.temporal_fwd(q, k, v, desc, out=nan(), lse=nan_lse())
+    grads = [nan(), nan(), nan()]
+    vc.vc_temporalattn_bwd(desc, q, k, v, o, lse, do, None, *grads, None, 0)
+    assert torch.equal(o, o1) and torch.equal(lse, lse1)
+    assert torch.equal(out, vc.branch_sum(desc, oj, os_, o))
+    so, slse = vc.spatial_fwd(q, k, v, desc, out=nan(), lse=nan_lse())
+    sdq = nan()
+    ws = vc.spatial_workspace(desc, "cuda")
+    vc.vc_spatialattn_bwd(desc, q, k, v, so, slse, do, None, None, sdq, nan(), nan(), ws, ws.numel())
+    for t in (o, *grads, so, sdq):
+        assert not bool(t[:, :text].any()) and bool(torch.isfinite(t).all())
+    for t in (lse, slse):
+        assert bool(torch.isneginf(t[:, :, :text]).all()) and bool(torch.isfinite(t[:, :, text:]).all())
