@@ -253,6 +253,17 @@ __global__ __launch_bounds__(64 * kDkdvWaves, 1) void bwd_dkdv_kernel(DkdvArgs a
     copy16_to_lds_opaque((is_q ? a.q : a.dout) + base + (size_t)tc.first * tok, tc.off,
                          (VC_LDS char*)smem + st * STAGE + (is_q ? 0 : RT) + (w % Lds::COPIES) * Rows::GS);
   };
+  // The dO rows past N - 1 that this wave copied into stage st: zero, as the probability 0 of such
+  // a row times an infinite dO of row N - 1, which it repeats, would be a NaN in dV. (Not where dQ
+  // is fused in, whose instances have no register left for it: 4 to 8 would spill.)
+  auto zero_do_padding = [&](int row0, int st) {
+    if (D == 64 && w < Lds::COPIES) return;
+    const int cl = fresh_lane(), idx = w % Lds::COPIES;
+    f32x4 z = {0.0f, 0.0f, 0.0f, 0.0f};
+    asm volatile("" : "+v"(z));  // formed here: no registers hold it across the walk
+    if (row0 + perm_row(Rows::RPC * idx + cl / Rows::CPR) >= N)
+      *(VC_LDS f32x4*)((VC_LDS char*)smem + st * STAGE + RT + idx * Rows::GS + 16 * cl) = z;
+  };
   // Query tiles this workgroup visits (the same sequence for every wave): all of them in
   // joint attention; in the spatial branch the video tiles its keys are attended from. The
   // host's spans count tiles of kTileTok queries.
@@ -406,6 +417,7 @@ __global__ __launch_bounds__(64 * kDkdvWaves, 1) void bwd_dkdv_kernel(DkdvArgs a
     for (int st = 0; qt < ntq; st ^= 1) {  // stage st holds tile qt, stage st ^ 1 takes the next
       const int qn = next_q(qt + 1);
       wait_all_memory();
+      if (!FUSED && qt * kBQ + kBQ > N) zero_do_padding(qt * kBQ, st);
       __syncthreads();
       if constexpr (DQ) {
         if (prev0 >= 0) {

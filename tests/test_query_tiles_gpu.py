@@ -55,6 +55,31 @@ def test_infinite_value_in_the_last_row(head_dim):
     assert_close("O", o[keep], ref[keep])
 
 
+@pytest.mark.parametrize("tokens", [131, 289])
+@pytest.mark.parametrize("head_dim", [64, 128])
+def test_infinite_output_gradient_in_the_last_row(head_dim, tokens):
+    """Separate dK/dV pass: the dO row of query N-1 stands in for the rows past N of the last tile of 32; those have
+    probability 0, which must not turn an infinite gradient into a NaN: dV is infinite in that
+    dim for every key (each has a positive probability), and the oracle's in every other."""
+    import torch
+    import paper_2501_08453_amd as vc
+    w = W.custom(1, 2, head_dim, 0, 1, 1, tokens)
+    x = W.make_inputs(w, seed=3)
+    g = {n: to_gpu_bf16(x[n]) for n in ("q", "k", "v", "do")}
+    do = bf16_values(g["do"])
+    do[0, -1, 1, 5] = 0.0
+    g["do"][0, -1, 1, 5] = float("inf")
+    desc = vc.desc_for(w, deterministic=True)
+    o, lse = vc.fwd(g["q"], g["k"], g["v"], desc)
+    _, _, dv = vc.bwd(g["q"], g["k"], g["v"], o, lse, g["do"], desc)
+    assert bool(torch.isposinf(dv[0, :, 1, 5]).all())
+    q, k, v = (bf16_values(g[n]) for n in ("q", "k", "v"))
+    _, _, ref = ora.attention_backward(q, k, v, do, np.ones((1, tokens), dtype=bool), ora.default_scale(head_dim))
+    keep = np.ones_like(ref, dtype=bool)
+    keep[0, :, 1, 5] = False
+    assert_close("dV", bf16_values(dv)[keep], ref[keep])
+
+
 @pytest.mark.parametrize("det", [False, True], ids=["fused", "deterministic"])
 @pytest.mark.parametrize("scale", [1e-30, 1e-37, 1e-39])
 def test_tiny_scale(scale, det):
