@@ -114,7 +114,12 @@ int64_t vc_jointattn_tokens(const vc_jointattn_desc* desc);
  * workgroups to end early: one per 256-row block, head and sample, at most 256,
  * or, where the best split of that round takes more, up to 512. A smaller
  * workspace is accepted down to the former number (fewer workgroups then share
- * the round; sums merged from another split round differently).
+ * the round; sums merged from another split round differently). A larger one than
+ * this changes no result.
+ * Which rows are split, and so how their sums round, follows from the shape, the batch
+ * included, and from the device's number of compute units: a sample's O, LSE and
+ * gradients agree bitwise with those of the same sample in another batch only where
+ * neither call splits its last round (else within the rounding of the sums).
  * 0 for an invalid descriptor. Host only. */
 size_t vc_jointattn_fwd_workspace_bytes(const vc_jointattn_desc* desc);
 
@@ -137,13 +142,15 @@ vc_status vc_jointattn_fwd(const vc_jointattn_desc* desc,
  * held from the library's first use on that device until the process ends. The
  * call itself allocates and frees nothing; on its first call on a device it looks
  * up that device's copy of the array (with that device current) and keeps the
- * address. Problems whose vc_jointattn_fwd_workspace_bytes exceed the array return
- * VC_ERR_SCRATCH before anything is launched (256 MiB holds, at head_dim 128, up to
+ * address. Problems whose least accepted forward workspace (see
+ * vc_jointattn_fwd_workspace_bytes) exceeds the array return VC_ERR_SCRATCH before
+ * anything is launched (256 MiB holds, at head_dim 128, up to
  * about 8.1e5 (sample, head, token) rows, e.g. 3 heads of 271k tokens; at head_dim 64
  * about 1.7e6). Every call on one device uses the same array: calls that overlap on a
  * device (other streams, other threads) race and must be serialised by the caller.
  * Nothing in the array needs clearing between calls: every byte read is written
- * first by the same call. Results are bitwise those of vc_jointattn_fwd.
+ * first by the same call. Results are bitwise those of vc_jointattn_fwd with a
+ * workspace of vc_jointattn_fwd_workspace_bytes or more.
  * ------------------------------------------------------------------------- */
 #define VC_JOINTATTN_NOALLOC_SCRATCH_BYTES ((size_t)256 << 20)
 

@@ -261,12 +261,15 @@ int64_t tail_wgs(size_t have, size_t used, size_t wg_bytes) {
   return have <= used ? 0 : std::min<int64_t>(kTailMaxWgs, (int64_t)((have - used) / wg_bytes));
 }
 
-// The same for the forward, whose plan must not depend on which entry point provides the
-// workspace where the no-allocation one accepts the problem (their outputs are bitwise equal).
-int64_t fwd_tail_wgs(const vc_jointattn_desc* d, int64_t n, size_t have) {
+// Plans of the three joint kernels in a workspace of `have` bytes. With the queried size or
+// more, on any number of compute units, a plan does not depend on `have` (no more split
+// workgroups are taken than the queried size holds), so results do not either; and where the
+// no-allocation forward accepts the problem, its scratch array and a workspace give one plan.
+TailPlan fwd_plan(const vc_jointattn_desc* d, int64_t n, int cus, size_t have) {
   if (fwd_ws_bytes(d, n) <= VC_JOINTATTN_NOALLOC_SCRATCH_BYTES)
     have = std::min<size_t>(have, VC_JOINTATTN_NOALLOC_SCRATCH_BYTES);
-  return tail_wgs(have, tiles_bytes(d, n), fwd_wg_bytes(d->head_dim));
+  return tail_plan(joint_items(d, n), ntiles(n), cus, kSplitFwd,
+                   std::min(queried_wgs(d, n, {kSplitFwd}), tail_wgs(have, tiles_bytes(d, n), fwd_wg_bytes(d->head_dim))));
 }
 
 // Backward workspace: -D | -LSE/c | fp32 dQ accumulator (in the place of three sets of token
@@ -284,8 +287,11 @@ size_t bwd_ws_query_bytes(const vc_jointattn_desc* d, int64_t n) {
   return bwd_ws_bytes(d, n) - tail_part_bytes(d, n) +
          align256(queried_wgs(d, n, {kSplitDkdv, kSplitDq}) * tail_wg_bytes(d->head_dim));
 }
-int64_t bwd_tail_wgs(const vc_jointattn_desc* d, int64_t n, size_t have) {
-  return tail_wgs(have, bwd_ws_bytes(d, n) - tail_part_bytes(d, n), tail_wg_bytes(d->head_dim));
+// `skip` key tiles are not visited by the dQ pass (their share of dQ is fused).
+TailPlan bwd_plan(const vc_jointattn_desc* d, int64_t n, int cus, SplitCost cost, int skip, size_t have) {
+  return tail_plan(joint_items(d, n), ntiles(n) - skip, cus, cost,
+                   std::min(queried_wgs(d, n, {kSplitDkdv, kSplitDq}),
+                            tail_wgs(have, bwd_ws_bytes(d, n) - tail_part_bytes(d, n), tail_wg_bytes(d->head_dim))));
 }
 float* tail_part_of(const vc_jointattn_desc* d, int64_t n, void* ws) {
   return reinterpret_cast<float*>(static_cast<char*>(ws) + 2 * rows_bytes(d, n) + 3 * tiles_bytes(d, n));
@@ -441,9 +447,7 @@ vc_status fwd_impl(const vc_jointattn_desc* desc, const void* q, const void* k, 
   a.ntile = ntiles(n);
   a.frame_len = spatial ? desc->grid_h * desc->grid_w : 0;
   a.scale_log2 = scale_of(desc) * vcja::kLog2e;
-  const TailPlan tp = spatial ? TailPlan{0, 1, 0}
-                              : tail_plan(joint_items(desc, n), ntiles(n), device_cus(), kSplitFwd,
-                                          fwd_tail_wgs(desc, n, workspace_bytes));
+  const TailPlan tp = spatial ? TailPlan{0, 1, 0} : fwd_plan(desc, n, device_cus(), workspace_bytes);
   a.tail_part = reinterpret_cast<float*>(static_cast<char*>(workspace) + tiles_bytes(desc, n));
   a.tail_blocks = tp.items;
   a.tail_chunks = tp.chunks;
@@ -537,9 +541,7 @@ vc_status dkdv_impl(const vc_jointattn_desc* desc, const void* q, const void* k,
   a.text_blocks = ts.blocks;
   a.text_chunks = ts.chunks;
   a.text_span = ts.span;
-  const TailPlan tp = spatial ? TailPlan{0, 1, 0}
-                              : tail_plan(joint_items(desc, n), ntiles(n), device_cus(), kSplitDkdv,
-                                          bwd_tail_wgs(desc, n, workspace_bytes));
+  const TailPlan tp = spatial ? TailPlan{0, 1, 0} : bwd_plan(desc, n, device_cus(), kSplitDkdv, 0, workspace_bytes);
   a.tail_part = tail_part_of(desc, n, workspace);
   a.tail_blocks = tp.items;
   a.tail_chunks = tp.chunks;
@@ -607,9 +609,7 @@ vc_status dq_impl(const vc_jointattn_desc* desc, const void* q, const void* k, c
   a.text_len = text_len;
   a.key_mask = key_mask;
   a.dq = static_cast<__bf16*>(dq);
-  const TailPlan tp = spatial ? TailPlan{0, 1, 0}
-                              : tail_plan(joint_items(desc, n), ntiles(n) - a.kt_min, device_cus(), kSplitDq,
-                                          bwd_tail_wgs(desc, n, workspace_bytes));
+  const TailPlan tp = spatial ? TailPlan{0, 1, 0} : bwd_plan(desc, n, device_cus(), kSplitDq, a.kt_min, workspace_bytes);
   a.tail_part = tail_part_of(desc, n, workspace);
   a.tail_blocks = tp.items;
   a.tail_chunks = tp.chunks;

@@ -1,7 +1,7 @@
 """GPU test of the no-allocation forward (vc_jointattn_fwd_noalloc), through the C ABI.
 
 Its output is compared with the workspace-taking forward's (vc_jointattn_fwd, the same
-kernels) bit for bit, and with the fp64 oracle to the parity bar, on two calls in a row,
+kernels, with its queried workspace) bit for bit, and with the fp64 oracle to the parity bar, on two calls in a row,
 the second with a smaller input: the ragged-text workload first (4 x 9,856 tokens, 216 MB
 of the 256 MiB scratch array), then a small ragged, key-masked problem at head_dim 64.
 A problem larger than the array is refused before anything runs.
@@ -11,7 +11,7 @@ import pytest
 
 import oracle.ref_attention as ora
 import workloads as W
-from parity_util import assert_close, bf16_values, log, to_gpu_bf16
+from parity_util import assert_close, bf16_values, log, lse_bound, to_gpu_bf16
 
 pytestmark = pytest.mark.gpu
 
@@ -70,3 +70,30 @@ def test_noalloc_forward_two_calls_then_refusal():
     with pytest.raises(vc.JointAttnError) as e:
         vc.vc_jointattn_fwd_noalloc(big, q, k, v, None, None, o, lse)
     assert e.value.status == -10
+
+
+@pytest.mark.parametrize("shape", [(1, 2, 64, 77, 3, 30, 61), (1, 13, 128, 16, 6, 30, 31), (1, 3, 128, 0, 1, 200, 200)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_noalloc_forward_where_the_last_round_is_split(shape):
+    """Split last rounds (44 items; 30 of 286; 215 of 471): bitwise the workspace-taking forward's
+    results with a workspace of the queried size or more; with the least accepted one, whose
+    fewer split workgroups round other sums, within two roundings of the LSE and 2^-7 of O's
+    2-norm (each side's probabilities are bf16, relative 2^-9 on average)."""
+    import torch
+    import paper_2501_08453_amd as vc
+    w = W.custom(*shape)
+    B, N, H, D = w.shape
+    gen = torch.Generator(device="cuda").manual_seed(N)
+    q, k, v = (torch.randn((B, N, H, D), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(3))
+    desc = vc.desc_for(w)
+    o_n, l_n = torch.empty_like(q), torch.empty((B, H, N), device="cuda")
+    vc.vc_jointattn_fwd_noalloc(desc, q, k, v, None, None, o_n, l_n)
+    need = vc.vc_jointattn_fwd_workspace_bytes(desc)
+    for size in (need, 2 * need + 12345):
+        o, lse = vc.fwd(q, k, v, desc, ws=torch.empty(size, dtype=torch.uint8, device="cuda"))
+        assert torch.equal(o, o_n) and torch.equal(lse, l_n)
+    up = lambda x: (x + 255) & ~255  # noqa: E731
+    least = up(B * H * ((N + 63) // 64) * D * 72 * 2) + up(min(256, (N + 255) // 256 * H * B) * 256 * (D + 2) * 4)
+    o, lse = vc.fwd(q, k, v, desc, ws=torch.empty(least, dtype=torch.uint8, device="cuda"))
+    assert float((lse - l_n).abs().max()) <= 2 * lse_bound(N)
+    assert float((o.float() - o_n.float()).norm() / o_n.float().norm()) <= 2.0 ** -7
