@@ -62,7 +62,7 @@ extern "C" {
 /* Raised with every change of a signature, a struct, the meaning of an argument or a
  * documented result; the Python binding refuses a library that reports another
  * version. */
-#define VC_JOINTATTN_ABI_VERSION 10
+#define VC_JOINTATTN_ABI_VERSION 11
 
 typedef enum vc_status {
   VC_OK = 0,
@@ -228,12 +228,13 @@ vc_status vc_jointattn_bwd_dq(const vc_jointattn_desc* desc,
  * that S and dP of those keys are computed once. Needs stage 1 on the same
  * workspace; stage 3 (vc_jointattn_bwd_dq with desc->deterministic = 0)
  * completes dq. */
-/* Keys [0, K) whose share of dq the fused pass adds (vc_jointattn_bwd_fused);
- * stage 3 covers keys [K, N). K is the leading 65% of the 256-key blocks at
- * head_dim 128 and every key at head_dim 64 (the fastest splits measured),
- * never more than N; 0 when a sample's N*H*D elements reach 2^32 (the fused
- * pass addresses its accumulator with 32-bit offsets). Returns K, or a negative
- * vc_status if the descriptor is invalid. Host only. */
+/* Keys [0, K) whose share of dq the fused stage adds (vc_jointattn_bwd_fused);
+ * stage 3 covers keys [K, N). This describes the staged calls: the one-call backward
+ * fuses every key's share of small problems (vc_jointattn_bwd). K is the leading 65% of
+ * the 256-key blocks at head_dim 128 and every key at head_dim 64, never more than N; 0
+ * when a sample's N*H*D elements reach 2^32 (the fused pass is used and tested below
+ * that size). Returns K, or a negative vc_status if the descriptor is invalid. Host
+ * only. */
 int64_t vc_jointattn_fused_dq_keys(const vc_jointattn_desc* desc);
 
 vc_status vc_jointattn_bwd_fused(const vc_jointattn_desc* desc,
