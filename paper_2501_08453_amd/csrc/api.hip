@@ -112,7 +112,9 @@ int ntiles(int64_t n) { return (int)((n + vcja::kTileTok - 1) / vcja::kTileTok);
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// Transposed token tiles of one [B, N, H, D] tensor.
+// Size of one [B, N, H, D] tensor in token-major tiles: what the workspaces are still sized by,
+// from versions that kept such copies (callers' sizes and the no-allocation forward's limit
+// stay as they were).
 size_t tiles_bytes(const vc_jointattn_desc* d, int64_t n) {
   return align256((size_t)d->batch * d->heads * ntiles(n) * vcja::tile_elems(d->head_dim) * sizeof(__bf16));
 }
@@ -130,7 +132,11 @@ size_t rows_bytes(const vc_jointattn_desc* d, int64_t n) {
 // of the merge launch, the round takes ceil(R C / cus) (span + over) + merge tiles instead
 // of ntile: the C of least time is taken, if it saves at least a tenth. Measured (tile =
 // 64 tokens; forward, dQ: about 2 us a tile, dK/dV 3.4 us, 8 to 13 us to write a
-// workgroup's partials, 6 to 15 us a merge): see kSplit*. `max_wgs` bounds R C (workspace).
+// workgroup's partials, 6 to 15 us a merge): see kSplit*. `max_wgs` bounds R C (workspace). At
+// head_dim 64 a tile takes about half of that and the same costs hold back splits that would
+// pay rather than take any that do not: at 25 shapes of 12 to 1,056 items no split lost (forward,
+// both backwards, us unsplit / split: 16 x 2,000 tokens 40 / 33, 105 / 79; 4 x 1,500 31 / 23, 76 /
+// 36; 5 x 20,000 680 / 614, 1906 / 1799), and costs 1.5 to 3 times as high lose such ones.
 struct SplitCost {
   int over, merge;
 };
@@ -194,9 +200,10 @@ size_t tail_part_bytes(const vc_jointattn_desc* d, int64_t n) {
 // (24 x 20,000 8144, 8471, 8380, 8023, 8401); the dQ pass then only converts the accumulator.
 constexpr int kFusedDqPercent128 = 65;
 constexpr int kFusedDqPercent64 = 100;
-// The fused pass addresses a sample's fp32 dQ accumulator with 32-bit element offsets, so it
-// runs only while a sample's N*H*D elements fit in 32 bits; larger inputs take the separate
-// passes.
+// The fused pass runs only while a sample's N*H*D elements number less than 2^32; larger inputs
+// take the separate passes. (Its addresses no longer need that bound: a uniform 64-bit base and
+// lane offsets of a few rows. It stays because no larger sample has been run or timed through
+// the atomics.)
 bool dq_offsets_fit(const vc_jointattn_desc* d, int64_t n) {
   return n * d->heads * d->head_dim < ((int64_t)1 << 32);
 }
@@ -249,7 +256,8 @@ bool spatial_fused(const vc_jointattn_desc* d, int64_t n, bool key_mask) {
           (n - d->text_slot) * d->heads * d->batch < kSpatialFusedRows);
 }
 
-// Forward workspace: V^T tiles | split-tail partials (unnormalised O, base, sum per row).
+// Forward workspace: one tensor's tiles (unused) | split-tail partials (unnormalised O, base, sum
+// per row).
 constexpr size_t fwd_wg_bytes(int head_dim) { return (size_t)kRowsPerItem * (head_dim + 2) * sizeof(float); }
 size_t fwd_tail_bytes(const vc_jointattn_desc* d, int64_t n) {
   const int64_t wgs = std::min<int64_t>(kTailMinWgs, joint_items(d, n));
@@ -532,7 +540,8 @@ vc_status dkdv_impl(const vc_jointattn_desc* desc, const void* q, const void* k,
       VC_OK)
     return st;
   if ((st = check_device()) != VC_OK) return st;
-  // The separate stages 2 and 3 belong to the deterministic backward.
+  // The separate stage 2 belongs to the deterministic backward; with the flag off it stays refused,
+  // as stage 3 would then look for an accumulator that it does not fill.
   if (staged && !desc->deterministic) return VC_ERR_UNSUPPORTED;
   const BwdWorkspace w = split_bwd_ws(desc, n, workspace);
   vcja::DkdvArgs a{};
@@ -637,7 +646,7 @@ vc_status bwd_impl(const vc_jointattn_desc* desc, const void* q, const void* k, 
   // dQ fused into the key-stationary kernel (atomics) unless the caller asks for bitwise
   // reproducible results: joint attention for its leading key blocks (the dQ pass covers
   // the others), the spatial branch, where it fuses, for every key block;
-  // neither past 32-bit dQ offsets.
+  // neither for samples of 2^32 elements or more.
   if (!desc->deterministic && (spatial ? spatial_fused(desc, n, key_mask != nullptr) : fused_dq_blocks(desc, n) > 0)) {
     if ((st = prepare_impl(desc, q, k, o, lse, dout, workspace, workspace_bytes, stream, true)) != VC_OK ||
         (st = dkdv_impl(desc, q, k, v, dout, text_len, key_mask, dk, dv, workspace, workspace_bytes, stream,

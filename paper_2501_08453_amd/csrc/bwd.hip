@@ -365,8 +365,8 @@ __global__ __launch_bounds__(64 * kDkdvWaves, 1) void bwd_dkdv_kernel(DkdvArgs a
   // (queries x keys) by transposing reads of dS^T, B = K from K^T. Lane l of 16-lane group G
   // supplies key 16*st + 8*hi + (l%16)/4 (+4), i.e. row 32*(st/2) + 4*(st%2) + 8*((l%16)/4) +
   // 2*hi (+1), and unit 4*(G%2) + l%4 of that row. The block is added to the accumulator with
-  // a uniform base plus a 32-bit per-lane offset (the host fuses dQ only when a sample's
-  // N*H*D elements fit in 32 bits); rows past N are padding.
+  // a uniform 64-bit base plus a 32-bit per-lane offset (4 rows at most); rows past N are
+  // padding.
   auto dq_step = [&](int row0, int buf) {
     const int ln = fresh_lane();
     const VC_LDS char* ds_src = (const VC_LDS char*)smem + Lds::DS_OFF + buf * Lds::DSB;

@@ -48,7 +48,8 @@ def test_tokens_and_workspace():
     al = lambda x: (x + 255) // 256 * 256  # noqa: E731
     rows = al(24 * npad * 4)
     tiles = al(24 * (npad // 64) * 128 * 72 * 2)
-    # V^T tiles, then per row of up to 256 split workgroups: fp32 O, base and sum
+    # the size of one tensor in token-major tiles, then per row of up to 256 split workgroups:
+    # fp32 O, base and sum
     assert vc.vc_jointattn_fwd_workspace_bytes(d3) == tiles + 256 * 256 * (128 + 2) * 4
     # fp32 partial dK, dV of up to 256 split workgroups of 256 keys (the last, partial round
     # of the 5,424 workgroups)
@@ -108,8 +109,8 @@ def test_fused_dq_keys():
         assert vc.vc_jointattn_fused_dq_keys(vc.make_desc(1, 1, 64, 0, 1, 1, 256 * n_blocks)) == 256 * n_blocks
         assert vc.vc_jointattn_fused_dq_keys(vc.make_desc(1, 1, 64, 0, 1, 1, 256 * n_blocks - 3)) == 256 * n_blocks - 3
     assert vc.vc_jointattn_fused_dq_keys(vc.make_desc(1, 1, 96, 0, 1, 1, 5)) == -3  # head_dim
-    # The fused pass addresses a sample's dQ accumulator with 32-bit offsets: none of it
-    # once N*H*D reaches 2^32 (here 1,166,656 tokens, 144 frames of 8,100 like the paper's
+    # The fused pass is used below 2^32 elements of a sample only: none of it once N*H*D
+    # reaches 2^32 (here 1,166,656 tokens, 144 frames of 8,100 like the paper's
     # 1.16M-token clip, at 32 heads; at 8 heads it stays below)
     big = vc.make_desc(1, 32, 128, 256, 144, 90, 90)
     n = vc.vc_jointattn_tokens(big)
@@ -263,7 +264,7 @@ def test_noalloc_forward_argument_errors(lib):
     assert lib.vc_jointattn_fwd_noalloc(None, p, p, p, None, None, p, p, None) == -1
     assert lib.vc_jointattn_fwd_noalloc(ctypes.byref(good_desc(head_dim=96)), p, p, p, None, None, p, p,
                                         None) == -3
-    long720p = vc.make_desc(1, 24, 128, 256, 16, 45, 80)  # 400 MB of V^T tiles
+    long720p = vc.make_desc(1, 24, 128, 256, 16, 45, 80)  # 434 MB
     assert vc.vc_jointattn_fwd_workspace_bytes(long720p) > vc.NOALLOC_SCRATCH_BYTES
     assert lib.vc_jointattn_fwd_noalloc(ctypes.byref(long720p), p, p, p, None, None, p, p, None) == -10
     assert "no-allocation" in vc.vc_status_string(-10)

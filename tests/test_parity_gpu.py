@@ -250,9 +250,8 @@ def test_long_workload_sampled():
 
 
 def test_long_workload_sampled_deterministic():
-    """Workload 3 with the deterministic backward (separate dK/dV pass with token-major Q and
-    dO copies, dQ pass over every key, both with their split last round and tail sums):
-    rows and columns of heads 0 and 23."""
+    """Workload 3 with the deterministic backward (separate dK/dV pass, dQ pass over every key,
+    both with their split last round and tail sums): rows and columns of heads 0 and 23."""
     _sampled_large(3, heads=[0, 23], n_rows=48, with_cols=True, det=True)
 
 
@@ -388,10 +387,11 @@ def test_backward_reproducibility():
 
 @pytest.mark.parametrize("head_dim", [128, 64])
 def test_staged_backward_calls(head_dim):
-    """The stage entry points reproduce vc_jointattn_bwd in both modes, and the separate
-    dK/dV stage refuses a descriptor of the fused backward (whose stage 1 does not make the
-    token-major copies it reads). With head_dim 64 the fused pass carries every key's dQ
-    (stage 3 then only converts the accumulator); with 128, the leading 65% of the keys'."""
+    """The stage entry points reproduce vc_jointattn_bwd in both modes (dQ of the fused one up to
+    the order of its sums), and the separate dK/dV stage refuses a descriptor of the fused
+    backward. With head_dim 64 the fused pass carries every key's dQ (stage 3 then only
+    converts the accumulator); with 128, the leading 65% of the keys' (the one call, for a
+    problem as small as this, every key's)."""
     import torch
     vc = _vc()
     w = W.custom(1, 2, head_dim, 24, 3, 9, 10, ragged_text=True)
