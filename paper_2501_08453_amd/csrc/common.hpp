@@ -60,13 +60,8 @@ typedef short i16x4 __attribute__((ext_vector_type(4)));
 
 // Asynchronous 16-byte copy global -> LDS: lane t of the wave writes its 16 bytes at
 // lds_wave_base + 16*t (lds_wave_base must be the same for the whole wave). Completion is
-// tracked by the vector-memory counter.
-__device__ __forceinline__ void copy16_to_lds(const void* g, VC_LDS void* lds_wave_base) {
-  __builtin_amdgcn_global_load_lds(g, lds_wave_base, 16, 0, 0);
-}
-
-// The same copy issued through inline assembly. The compiler then does not know that the
-// instruction writes LDS, so it inserts no wait for it before later LDS reads: it would
+// tracked by the vector-memory counter. Issued through inline assembly: the compiler then does
+// not know that the instruction writes LDS, so it inserts no wait for it before later LDS reads: it would
 // otherwise wait for every copy in flight before any read whose address it cannot prove
 // distinct from the copies' (the ring's other stage, in practice). The caller waits for
 // the copies (wait_all_memory) before reading what they write. Sets M0; a kernel using it
@@ -79,7 +74,10 @@ __device__ __forceinline__ void copy16_to_lds_opaque(const void* g, VC_LDS void*
 }
 
 // The same from a wave-uniform base plus a 32-bit byte offset per lane, so that a copy whose
-// lanes keep their offsets from tile to tile needs scalar address arithmetic only.
+// lanes keep their offsets from tile to tile needs scalar address arithmetic only. (The compiler
+// does not see that the copy reads `base`'s scalar registers: a vector instruction that writes
+// them, such as the reload of a spilled scalar, must lie 5 wait states ahead, of which this
+// sequence gives 2. tests/test_kernel_asm.py looks for nearer ones in every kernel.)
 __device__ __forceinline__ void copy16_to_lds_opaque(const void* base, unsigned lane_off, VC_LDS void* lds_wave_base) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                :

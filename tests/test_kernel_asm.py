@@ -4,6 +4,9 @@ hipcc cross-compiles the device code to assembly).
 - The inline-assembly LDS copies set M0 themselves; a kernel that uses them must not rely on
   M0 anywhere else. Every M0 write must therefore be one copy's own, right before its
   global -> LDS instruction, and every such instruction must come from those copies.
+- A copy's scalar base is not written by a vector instruction (the reload of a spilled scalar)
+  within the 5 wait states before it that the hardware needs: the compiler, which does not
+  look into inline assembly, does not keep them.
 - Packed fp32 arithmetic is disabled at build time; no packed fp32 add, multiply or fma may
   appear in any kernel.
 - The hot joint-attention kernels and the long-clip temporal kernels fit their register
@@ -78,6 +81,48 @@ def test_m0_is_set_only_by_the_lds_copies(device_asm):
                     assert prev and prev[-1].startswith("s_mov_b32 m0,"), (fn, name, ins[max(0, i - 2):i + 1])
                     seen_copies += 1
     assert seen_copies > 0  # the forward, dK/dV and dQ kernels all copy tiles this way
+
+
+def scalar_registers(operand):
+    """Numbers of the scalar registers an operand names."""
+    m = re.match(r"s\[(\d+):(\d+)\]|s(\d+)$", operand)
+    if not m:
+        return set()
+    lo = int(m.group(1) or m.group(3))
+    return set(range(lo, int(m.group(2) or lo) + 1))
+
+
+def late_scalar_writes(ins, need=5):
+    """(writer, copy) pairs where a vector instruction writes a scalar register that an LDS copy
+    reads fewer than `need` wait states later (an instruction is one, s_nop n is n + 1)."""
+    found = []
+    for i, line in enumerate(ins):
+        if not line.startswith("global_load_lds"):
+            continue
+        reads = set().union(*(scalar_registers(x.strip().split(" ")[0]) for x in line.split(None, 1)[1].split(",")))
+        states = 0
+        for prev in reversed(ins[:i]):
+            if states >= need:
+                break
+            op, _, args = prev.partition(" ")
+            if op.startswith("v_") and scalar_registers(args.split(",")[0].strip()) & reads:
+                found.append((prev, line))
+            states += int(args) + 1 if op == "s_nop" else 1
+    return found
+
+
+def test_scalar_bases_of_the_lds_copies_are_settled(device_asm):
+    copy = ["s_mov_b32 m0, s9", "s_nop 0", "global_load_lds_dwordx4 v1, s[2:3]"]
+    for n, late in ((0, True), (1, True), (2, True), (3, False)):  # the detector itself
+        assert bool(late_scalar_writes(["v_readlane_b32 s3, v9, 4"] + ["s_add_i32 s8, s8, 1"] * n + copy)) == late
+    assert not late_scalar_writes(["v_readlane_b32 s4, v9, 4"] + copy)
+    with_base = 0
+    for fn, text in device_asm.items():
+        for name, body in kernels(text):
+            ins = list(instructions(body))
+            with_base += sum(bool(re.match(r"global_load_lds_dwordx4 v\d+, s\[", x)) for x in ins)
+            assert not late_scalar_writes(ins), (fn, name, late_scalar_writes(ins)[:2])
+    assert with_base > 0
 
 
 def test_no_packed_fp32_arithmetic(device_asm):
