@@ -417,7 +417,7 @@ __global__ __launch_bounds__(64 * kDkdvWaves, 1) void bwd_dkdv_kernel(DkdvArgs a
     for (int st = 0; qt < ntq; st ^= 1) {  // stage st holds tile qt, stage st ^ 1 takes the next
       const int qn = next_q(qt + 1);
       wait_all_memory();
-      if (!FUSED && qt * kBQ + kBQ > N) zero_do_padding(qt * kBQ, st);
+      if (!FUSED && __builtin_expect(qt * kBQ + kBQ > N, 0)) zero_do_padding(qt * kBQ, st);
       __syncthreads();
       if constexpr (DQ) {
         if (prev0 >= 0) {
