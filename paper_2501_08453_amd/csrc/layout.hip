@@ -24,28 +24,37 @@ __global__ void zero_f32_kernel(float* x, size_t n4) {
 }
 
 template <int D>
-__global__ __launch_bounds__(256) void text_rows_kernel(TextRows t, int B, int H, int N, int T) {
-  write_text_rows<D>(t, B, H, N, T, threadIdx.x, blockIdx.x, gridDim.x);
+__global__ __launch_bounds__(256) void text_rows_kernel(TextRows t, int H, int N, int T) {
+  const size_t first = (size_t)blockIdx.y * N * H * D;  // sample blockIdx.y alone: no division by its chunks
+  t.x0 += first;
+  if (t.x1) t.x1 += first;
+  if (t.x2) t.x2 += first;
+  if (t.lse) t.lse += (size_t)blockIdx.y * H * N;
+  if (t.sum_a) t.sum_a += first;
+  if (t.sum_b) t.sum_b += first;
+  if (t.sum) t.sum += first;
+  write_text_rows<D>(t, 1, H, N, T, threadIdx.x, blockIdx.x, gridDim.x);
 }
 
 }  // namespace
 
-// In the branch's grid up to 16 chunks a thread, up to 8 with a sum, whose reads a thread waits
-// for. Measured, us a call, in the grid / apart: temporal forward at 3.6 chunks 7.6 / 10.3, 11
-// 9.7 / 10.0, 21 11.8 / 10.1, 64 25.8 / 9.9; with the sum 9.4 / 13.3, 17.3 / 16.7, 17.1 / 13.4,
-// 38.2 / 13.3; backward at 11 9.8 / 10.7, 32 12.3 / 10.8; spatial forward at 16 49.5 / 50.8, 128
-// 159 / 117.
+// In the branch's grid up to 24 chunks a thread, up to 16 with an LSE, whose index takes a
+// division, and up to 8 with a sum, whose reads a thread waits for. Measured, us a call, in the grid
+// / apart: temporal forward at 3.6 chunks 8.2 / 11.1, 13 9.7 / 10.5, 21 11.8 / 10.4, 64 24.3 / 10.8;
+// with the sum at 3.6 9.7 / 10.9, 8 21.0 / 22.5, 11 12.1 / 10.7, 43 27.3 / 10.7; backward at 11 10.1 /
+// 11.2, 21 11.8 / 11.2 and 9.4 / 11.3, 28 18.8 / 21.1, 32 12.0 / 11.2; spatial forward at 8 218.9 /
+// 219.2, 21 67.1 / 63.4, 128 159 / 117, its backward at 21 108.2 / 108.7.
 hipError_t place_text_rows(const TextRows& t, int B, int H, int N, int T, int head_dim, size_t threads, hipStream_t s,
                            int* in_grid) {
-  const size_t chunks = (size_t)B * T * H * (head_dim / 8);
-  const bool apart = chunks > (t.sum ? 8 : 16) * threads;
+  const size_t per = (size_t)T * H * (head_dim / 8);
+  const bool apart = B * per > (t.sum ? 8 : t.lse ? 16 : 24) * threads;
   *in_grid = apart ? 0 : T;
   if (!apart) return hipSuccess;
-  const dim3 grid((unsigned)std::min<size_t>((chunks + 255) / 256, 1 << 20));
+  const dim3 grid((unsigned)std::min<size_t>((per + 255) / 256, 1 << 20), B);
   if (head_dim == 128)
-    hipLaunchKernelGGL(text_rows_kernel<128>, grid, dim3(256), 0, s, t, B, H, N, T);
+    hipLaunchKernelGGL(text_rows_kernel<128>, grid, dim3(256), 0, s, t, H, N, T);
   else
-    hipLaunchKernelGGL(text_rows_kernel<64>, grid, dim3(256), 0, s, t, B, H, N, T);
+    hipLaunchKernelGGL(text_rows_kernel<64>, grid, dim3(256), 0, s, t, H, N, T);
   return hipGetLastError();
 }
 
